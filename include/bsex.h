@@ -456,9 +456,8 @@ int bse_learned_features(bse_ctx *ctx, const double *Xs_dev, const double *Zref_
  * alone).  Each system's tau cache is capped at its own size.  With autotune,
  * the Davidson block apply of each shape class (grid, N_v in buckets of 64,
  * precision) that occurs more than once in the batch is timed under each
- * kernel variant (compile-time or runtime FFT kernels; 4 or 2 lanes per grid
- * point in the tau stream; one warm-up, two timed applies each) and the
- * fastest is cached for the process; a class met once keeps the defaults.
+ * kernel variant (compile-time or runtime FFT kernels; one warm-up, two timed
+ * applies each) and the fastest is cached for the process; a class met once keeps the defaults.
  * desc.stream and desc.precision are ignored (the batch's are used).
  */
 typedef struct {
@@ -476,8 +475,8 @@ typedef struct {
   double *dwdR_host;          /* caller's [n_sites][3] output, or NULL             */
   int32_t davidson_iters, z_iters;
   double t_init_ms, t_davidson_ms, t_z_ms, t_force_ms;
-  int32_t variant;            /* autotuned variant (bit 0: runtime FFT kernels,
-                                 bit 1: 2 lanes per point), -1 when not tuned     */
+  int32_t variant;            /* autotuned variant (bit 0: runtime FFT kernels),
+                                 -1 when not tuned                                */
   int32_t stream_slot;        /* stream (worker) that ran it                       */
   char message[160];          /* error text when status != BSE_OK                  */
 } bse_batch_result;

@@ -29,12 +29,8 @@ namespace {
 // stack of each slot thread (solver host code, HIP runtime, profiler callbacks)
 constexpr size_t kSlotStack = (size_t)64 << 20;
 
-// variant bits: 1 = runtime-length FFT kernels, 2 = the tau stream whose four
-// lanes per grid point each read whole blocks (instead of quad-shared loads)
-void set_variant(bse_ctx* c, int v) {
-  fft_plan_set_runtime(&c->fft, (v & 1) != 0);
-  c->tau_bl = (v & 2) ? 4 : 1;
-}
+// variant bits: 1 = runtime-length FFT kernels
+void set_variant(bse_ctx* c, int v) { fft_plan_set_runtime(&c->fft, (v & 1) != 0); }
 
 using TuneKey = std::tuple<int, int, int, int, int, int>;
 std::mutex g_tune_mu;
@@ -91,7 +87,7 @@ int autotune(bse_ctx* c, int nb, int* chosen, double* best_ms) {
   int best = 0;
   double bms = 1e300;
   if (rc == BSE_OK) rc = apply_any(c, nb, X, Y);  // warm-up (and lazy buffers)
-  for (int v = 0; v < 4 && rc == BSE_OK; ++v) {
+  for (int v = 0; v < 2 && rc == BSE_OK; ++v) {
     if ((v & 1) && !ct) continue;  // no compile-time FFT to switch off
     set_variant(c, v);
     double ms = 0.0;

@@ -350,19 +350,13 @@ __global__ __launch_bounds__(256) void k_tau_store_lds(const G2* __restrict__ gr
 // with tau stored once per unordered pair as 8x8 blocks (diagonal blocks hold
 // the upper triangle with the diagonal halved), blocks in row-major order of
 // the block triangle.  A workgroup owns R grid points; a and the y
-// accumulators of those points live in LDS.  The NBT = 8 trial vectors are
-// split over BL adjacent lanes; a unit of BL lanes owns one grid point and a
-// contiguous run of blocks, so along a run the row block I changes rarely:
-// its accumulator y[I] and a[I] stay in registers and are flushed to LDS only
-// when I changes, while the transposed contribution y[J] goes to LDS with one
-// atomic add per (j, b).
+// accumulators of those points live in LDS.  The NBT = 4 NBL trial vectors are
+// split over the four lanes of a DPP quad; a slot of 4 R lanes owns a
+// contiguous run of blocks at the R points, so along a run the row block I
+// changes rarely: its accumulator y[I] and a[I] stay in registers and are
+// flushed to LDS only when I changes, while the transposed contribution y[J]
+// goes to LDS with one atomic add per (j, b).
 // ---------------------------------------------------------------------------
-constexpr int NBT = 8;
-constexpr int NSLOT = 128;
-
-// FUSE: the epilogue writes z = V a + s (v_c*Drho_b) phi - y instead of y
-// (into `y`, which may alias `a`: every workgroup reads its points of a into
-// LDS before any write and no other workgroup touches them).
 template <typename T>
 struct vec2_of;
 template <>
@@ -374,150 +368,12 @@ struct vec2_of<float> {
   using type = float2;
 };
 
-// LDS rows (one per orbital v) hold NBT * R values plus SPAD of padding: the
-// slots of a wave work on unrelated rows, and an unpadded row of 16 words
-// would put the same word of every row in the same bank.  A launch stages the
-// rows row0 .. row0 + nrows - 1 only: the bands its blocks touch (a rebuilt
-// tile late in the block order touches only the last bands).
-constexpr int SPAD = 1;
-
-// T: storage and arithmetic type of tau, a and y.  The LDS accumulators of y
-// are FP64 for both types: the LDS FP32 atomic add is several times slower
-// than the FP64 one on gfx950, and FP64 sums lose nothing.
-template <int R, int BL, bool FUSE, typename T>
-__global__ __launch_bounds__(NSLOT * R * BL) void k_tau_stream(
-    const T* __restrict__ tau, long rb_stride, long nblk, const int2* __restrict__ IJ,
-    const typename vec2_of<T>::type* a, typename vec2_of<T>::type* y, int nb, int nv, int nvh,
-    long nr, int row0, int nrows, int accumulate, const T* __restrict__ V,
-    const typename vec2_of<T>::type* __restrict__ vdrho,
-    const typename vec2_of<T>::type* __restrict__ phir, T s, int with_v) {
-  using V2 = typename vec2_of<T>::type;
-  constexpr int NT = NSLOT * R * BL;
-  constexpr int NBL = NBT / BL;
-  constexpr int RS = NBT * R + SPAD;
-  // rows of a tau block loaded ahead of their use: the whole block in FP32
-  // (64 registers), two rows in FP64
-  constexpr int JU = sizeof(T) == 4 ? 8 : 2;
-  extern __shared__ char lds_raw[];
-  T* as = reinterpret_cast<T*>(lds_raw);
-  double* ys = reinterpret_cast<double*>(as + (long)nrows * RS);
-  const long rb = blockIdx.x;
-  const long r0 = rb * R;
-  const int n_el = nrows * NBT * R;
-  for (int e = threadIdx.x; e < n_el; e += NT) {
-    const int ri = e % R;
-    const int b = (e / R) % NBT;
-    const int vl = e / (R * NBT);
-    const int v = row0 + vl;
-    T av = 0;
-    double yv = 0;
-    if (v < nv && b < nb) {
-      const long gi = ((long)b * nvh + (v >> 1)) * nr + r0 + ri;
-      av = reinterpret_cast<const T*>(a + gi)[v & 1];
-      if (accumulate) yv = reinterpret_cast<const T*>(y + gi)[v & 1];
-    }
-    const int li = vl * RS + b * R + ri;
-    as[li] = av;
-    ys[li] = yv;
-  }
-  __syncthreads();
-  const int bl = threadIdx.x % BL;
-  const int ri = (threadIdx.x / BL) % R;
-  const int slot = threadIdx.x / (BL * R);
-  const long b0 = nblk * slot / NSLOT, b1 = nblk * (slot + 1) / NSLOT;
-  const T* tb = tau + rb * rb_stride + ri * 8;
-  const int lo = bl * NBL * R + ri;  // lane offset inside an LDS row
-  int curI = -1;
-  T aI[8][NBL], acc[8][NBL];
-  for (long blk = b0; blk < b1; ++blk) {
-    const int2 bij = IJ[blk];
-    if (bij.x != curI) {
-      if (curI >= 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int b = 0; b < NBL; ++b)
-            atomicAdd(&ys[(curI * 8 + i - row0) * RS + lo + b * R], (double)acc[i][b]);
-      }
-      curI = bij.x;
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int b = 0; b < NBL; ++b) {
-          aI[i][b] = as[(curI * 8 + i - row0) * RS + lo + b * R];
-          acc[i][b] = 0;
-        }
-    }
-    const T* tp = tb + blk * 64 * R;
-#pragma unroll 1
-    for (int j0 = 0; j0 < 8; j0 += JU) {
-      T t[JU][8];
-#pragma unroll
-      for (int jj = 0; jj < JU; ++jj)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t[jj][i] = tp[(j0 + jj) * 8 * R + i];
-#pragma unroll
-      for (int jj = 0; jj < JU; ++jj) {
-        const int wv = bij.y * 8 + j0 + jj - row0;
-        T aj[NBL], tr[NBL];
-#pragma unroll
-        for (int b = 0; b < NBL; ++b) {
-          aj[b] = as[wv * RS + lo + b * R];
-          tr[b] = 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int b = 0; b < NBL; ++b) {
-            acc[i][b] = fma(t[jj][i], aj[b], acc[i][b]);
-            tr[b] = fma(t[jj][i], aI[i][b], tr[b]);
-          }
-#pragma unroll
-        for (int b = 0; b < NBL; ++b) atomicAdd(&ys[wv * RS + lo + b * R], (double)tr[b]);
-      }
-    }
-  }
-  if (curI >= 0) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int b = 0; b < NBL; ++b)
-        atomicAdd(&ys[(curI * 8 + i - row0) * RS + lo + b * R], (double)acc[i][b]);
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < n_el; e += NT) {
-    const int rr = e % R;
-    const int b = (e / R) % NBT;
-    const int vl = e / (R * NBT);
-    const int v = row0 + vl;
-    if (v < nv && b < nb) {
-      const long gi = ((long)b * nvh + (v >> 1)) * nr + r0 + rr;
-      const int li = vl * RS + b * R + rr;
-      T out = (T)ys[li];
-      if (FUSE) {
-        const long r = r0 + rr;
-        T z = -out;
-        if (with_v) z += V[r] * as[li];
-        if (vdrho) {
-          const T d = reinterpret_cast<const T*>(vdrho + (long)(b >> 1) * nr + r)[b & 1];
-          const T f = reinterpret_cast<const T*>(phir + (long)(v >> 1) * nr + r)[v & 1];
-          z += s * d * f;
-        }
-        out = z;
-      }
-      reinterpret_cast<T*>(y + gi)[v & 1] = out;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Quad-shared tau stream (the default).  The work layout of k_tau_stream with
-// four lanes per grid point (lane bl takes trial vectors 2bl, 2bl+1), but each
-// lane reads only columns 2bl and 2bl+1 of a block from memory and the block's
-// eight columns reach all four lanes of the quad by DPP broadcasts: every tau
-// value leaves the cache once, and the LDS traffic is that of k_tau_stream.
-// ---------------------------------------------------------------------------
-constexpr int QS_BL = 4;
+// LDS rows (one per orbital v) hold NBT * R values in [ri][b] order plus pad
+// values (tau_stream_row): the slots of a wave work on unrelated rows, and a
+// row of a power of two would put the same word of every row in the same
+// bank.  A launch stages the rows row0 .. row0 + nrows - 1 only: the bands its
+// blocks touch (a rebuilt tile late in the block order touches only the last
+// bands).
 
 // Workgroup i runs on XCD i mod 8 (round-robin dispatch).  Give each XCD a
 // contiguous range of grid-point blocks, in order, so the workgroups whose
@@ -543,180 +399,292 @@ __device__ __forceinline__ double quad_bcast(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-__device__ __forceinline__ void load8(double (&v)[8], const double* p) {
-  const double2* q = reinterpret_cast<const double2*>(p);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const double2 w = q[k];
-    v[2 * k] = w.x;
-    v[2 * k + 1] = w.y;
+// The four lanes of a quad read a block in 16-byte chunks: 8 chunks of one
+// column in FP64 (lane bl holds rows 2bl, 2bl+1), 4 chunks of two columns in
+// FP32 (lane bl holds rows 4(bl & 1) .. +3 of the chunk's column bl >> 1), so
+// the 4 R lanes of a slot read each chunk as one contiguous run.
+template <typename T>
+struct TauChunk;
+template <>
+struct TauChunk<double> {
+  using type = double2;
+  static constexpr int N = 8, COLS = 1;
+  static __device__ __forceinline__ int lane_off(int bl, int ri, int R) { return ri * 8 + 2 * bl; }
+  // element (i, column C of the chunk)
+  template <int I, int C>
+  static __device__ __forceinline__ double get(const double2& v) {
+    return quad_bcast<I / 2>(I % 2 ? v.y : v.x);
   }
-}
-__device__ __forceinline__ void load8(float (&v)[8], const float* p) {
-  const float4* q = reinterpret_cast<const float4*>(p);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float4 w = q[k];
-    v[4 * k] = w.x;
-    v[4 * k + 1] = w.y;
-    v[4 * k + 2] = w.z;
-    v[4 * k + 3] = w.w;
+};
+template <>
+struct TauChunk<float> {
+  using type = float4;
+  static constexpr int N = 4, COLS = 2;
+  static __device__ __forceinline__ int lane_off(int bl, int ri, int R) {
+    return (bl >> 1) * 8 * R + ri * 8 + 4 * (bl & 1);
+  }
+  template <int I, int C>
+  static __device__ __forceinline__ float get(const float4& v) {
+    return quad_bcast<2 * C + I / 4>(I % 4 == 0 ? v.x : I % 4 == 1 ? v.y : I % 4 == 2 ? v.z : v.w);
+  }
+};
+
+template <typename T, int NBL>
+__device__ __forceinline__ void lds_vec(T (&v)[NBL], const T* p) {
+  if constexpr (NBL == 2) {
+    const typename vec2_of<T>::type w = *reinterpret_cast<const typename vec2_of<T>::type*>(p);
+    v[0] = w.x;
+    v[1] = w.y;
+  } else {
+    v[0] = p[0];
   }
 }
 
-// one column j of the current block: t[i] = tau[i][j] from the quad lane that
-// read it, then acc (row block I) and the transposed contribution to row j
-template <int J, int R, typename T>
-__device__ __forceinline__ void qs_column(const T (&own)[2][8], T (&acc)[8][2],
-                                          const T (&aI)[8][2], const T* as, double* ys,
-                                          int rowJ, int lo) {
-  constexpr int NBL = 2;
-  constexpr int RS = NBT * R + SPAD;
-  T t[8];
+// one column of the current block (t[i] = tau[i][j]): acc (row block I) and
+// the transposed contribution to row j.  Two halves of four rows: with all
+// eight t[i] broadcast at once the FP64 loop needs more than the 128
+// registers that four waves per SIMD leave, and its spills wait for the
+// block in flight.
+template <int C, int H, int NBL, typename T, typename CH>
+__device__ __forceinline__ void qs_half(const CH& own, T (&acc)[8][NBL], const T (&aI)[8][NBL],
+                                        const T (&aj)[NBL], T (&tr)[NBL]) {
+  using TC = TauChunk<T>;
+  const T t[4] = {TC::template get<4 * H, C>(own), TC::template get<4 * H + 1, C>(own),
+                  TC::template get<4 * H + 2, C>(own), TC::template get<4 * H + 3, C>(own)};
 #pragma unroll
-  for (int i = 0; i < 8; ++i) t[i] = quad_bcast<J / 2>(own[J % 2][i]);
-  const int wv = rowJ + J;
-  T aj[NBL], tr[NBL];
-#pragma unroll
-  for (int b = 0; b < NBL; ++b) {
-    aj[b] = as[wv * RS + lo + b * R];
-    tr[b] = 0;
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int b = 0; b < NBL; ++b) {
-      acc[i][b] = fma(t[i], aj[b], acc[i][b]);
-      tr[b] = fma(t[i], aI[i][b], tr[b]);
+      acc[4 * H + i][b] = fma(t[i], aj[b], acc[4 * H + i][b]);
+      tr[b] = fma(t[i], aI[4 * H + i][b], tr[b]);
     }
+}
+template <int C, int NBL, typename T, typename CH>
+__device__ __forceinline__ void qs_column(const CH& own, T (&acc)[8][NBL], const T (&aI)[8][NBL],
+                                          const T* as, double* ys) {
+  T aj[NBL], tr[NBL];
+  lds_vec<T, NBL>(aj, as);
 #pragma unroll
-  for (int b = 0; b < NBL; ++b) atomicAdd(&ys[wv * RS + lo + b * R], (double)tr[b]);
+  for (int b = 0; b < NBL; ++b) tr[b] = 0;
+  qs_half<C, 0, NBL>(own, acc, aI, aj, tr);
+  __builtin_amdgcn_sched_barrier(0);
+  qs_half<C, 1, NBL>(own, acc, aI, aj, tr);
+#pragma unroll
+  for (int b = 0; b < NBL; ++b) atomicAdd(&ys[b], (double)tr[b]);
 }
 
-template <int R, bool FUSE, typename T>
-__global__ __launch_bounds__(NSLOT * R * QS_BL) void k_tau_stream_qs(
+// What bounds it: HBM for one vector (64^3, N_v = 200: 6.1 TB/s); for a block
+// of 8 the LDS atomics and the FP64 (FP32) multiply-adds, each about half the
+// cycles, beside an HBM stream of 5.2 (4.2) TB/s (72^3, N_v = 432).  Reading
+// whole columns per lane (four separate lines per load) and waiting for each
+// block before using it, the same work took 65.0 (40.4) ms there against 58.7
+// (36.0) now, and in one shape of 128 slots 0.091 against 0.017 ms at 24^3,
+// N_v = 16 (5 vectors) and 13.4 against 10.6 ms at 64^3, N_v = 200.
+// Broadcasts folded into the FP32 multiply-adds (v_fmac_f32 with a DPP
+// operand) were no faster (36.0 against 35.6 ms, 10.6 against 10.9 at 60^3,
+// N_v = 300).
+//
+// T: storage and arithmetic type of tau, a and y.  The LDS accumulators of y
+// are FP64 for both types: the LDS FP32 atomic add is several times slower
+// than the FP64 one on gfx950, and FP64 sums lose nothing.
+//
+// FUSE: the epilogue writes z = V a + s (v_c*Drho_b) phi - y instead of y
+// (into `y`, which may alias `a`: every workgroup reads its points of a into
+// LDS before any write and no other workgroup touches them).
+//
+// VRUNS: the FP32 sums of a row block are flushed to the FP64 accumulators at
+// the ends of 128 equal runs of blocks, whatever the number of slots, so the
+// roundings do not depend on the launch shape.
+constexpr int VRUNS = 128;
+
+template <int R, int NT, int NBL, bool FUSE, typename T>
+__global__ __launch_bounds__(NT, 4) void k_tau_stream_qs(
     const T* __restrict__ tau, long rb_stride, long nblk, const int2* __restrict__ IJ,
     const typename vec2_of<T>::type* a, typename vec2_of<T>::type* y, int nb, int nv, int nvh,
-    long nr, int row0, int nrows, int accumulate, const T* __restrict__ V,
+    long nr, int row0, int nrows, int rs, int accumulate, const T* __restrict__ V,
     const typename vec2_of<T>::type* __restrict__ vdrho,
     const typename vec2_of<T>::type* __restrict__ phir, T s, int with_v) {
-  constexpr int NT = NSLOT * R * QS_BL;
-  constexpr int NBL = NBT / QS_BL;
-  constexpr int RS = NBT * R + SPAD;
+  using V2 = typename vec2_of<T>::type;
+  using TC = TauChunk<T>;
+  using CH = typename TC::type;
+  constexpr int NBT = 4 * NBL;
+  constexpr int NS = NT / (4 * R);  // slots
+  constexpr bool RUNS = sizeof(T) == 4;
+  static_assert(!RUNS || VRUNS % NS == 0, "slots must nest in the runs");
   extern __shared__ char lds_raw[];
-  T* as = reinterpret_cast<T*>(lds_raw);
-  double* ys = reinterpret_cast<double*>(as + (long)nrows * RS);
+  double* ys = reinterpret_cast<double*>(lds_raw);
+  T* as = reinterpret_cast<T*>(ys + (long)nrows * rs);
   const long rb = xcd_order(blockIdx.x, gridDim.x);
   const long r0 = rb * R;
-  const int n_el = nrows * NBT * R;
-  for (int e = threadIdx.x; e < n_el; e += NT) {
-    const int ri = e % R;
-    const int b = (e / R) % NBT;
-    const int vl = e / (R * NBT);
-    const int v = row0 + vl;
-    T av = 0;
-    double yv = 0;
-    if (v < nv && b < nb) {
-      const long gi = ((long)b * nvh + (v >> 1)) * nr + r0 + ri;
-      av = reinterpret_cast<const T*>(a + gi)[v & 1];
-      if (accumulate) yv = reinterpret_cast<const T*>(y + gi)[v & 1];
+  // Staging and epilogue: a thread keeps one (point, vector) and walks the
+  // pairs of bands (one packed grid value each), ST of them in flight.  With
+  // the indices divided out per element and one load at a time these phases
+  // were a fifth of the kernel's vector instructions at 72^3, N_v = 432
+  // (FP32 48^3, N_v = 180: 2.16 ms, now 1.97).
+  constexpr int PS = NT / (R * NBT), ST = 4;
+  const long own0 = (long)(row0 / 2) * nr + r0;  // this workgroup's first value: read where
+                                                 // a lane has none of its own
+  struct Walk {
+    int b, sp, ri, npair, vpair, li, lstep;
+    long g, gstep;
+  };
+  auto walk = [&](int t) {
+    Walk w;
+    w.ri = t % R;
+    w.b = (t / R) % NBT;
+    w.sp = t / (R * NBT);
+    w.npair = nrows / 2;
+    w.vpair = w.b < nb ? min(w.npair, (nv - row0 + 1) / 2) : 0;  // pairs that hold bands
+    w.g = ((long)w.b * nvh + row0 / 2 + w.sp) * nr + r0 + w.ri;
+    w.gstep = (long)PS * nr;
+    w.li = 2 * w.sp * rs + w.ri * NBT + w.b;
+    w.lstep = 2 * PS * rs;
+    return w;
+  };
+  {
+    Walk w = walk(threadIdx.x);
+    for (int pl = w.sp; pl < w.npair; pl += ST * PS, w.g += ST * w.gstep) {
+      V2 x[ST], q[ST];
+#pragma unroll
+      for (int u = 0; u < ST; ++u) {
+        const bool ok = pl + u * PS < w.vpair;
+        x[u] = a[ok ? w.g + u * w.gstep : own0];
+        if (!ok) x[u].x = x[u].y = 0;
+        q[u].x = q[u].y = 0;
+      }
+      if (accumulate) {
+#pragma unroll
+        for (int u = 0; u < ST; ++u) {
+          const bool ok = pl + u * PS < w.vpair;
+          q[u] = y[ok ? w.g + u * w.gstep : own0];
+          if (!ok) q[u].x = q[u].y = 0;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < ST; ++u)
+        if (pl + u * PS < w.npair) {
+          const bool two = row0 + 2 * (pl + u * PS) + 1 < nv;  // both bands exist
+          as[w.li] = x[u].x;
+          as[w.li + rs] = two ? x[u].y : (T)0;
+          ys[w.li] = q[u].x;
+          ys[w.li + rs] = two ? q[u].y : (T)0;
+          w.li += w.lstep;
+        }
     }
-    const int li = vl * RS + b * R + ri;
-    as[li] = av;
-    ys[li] = yv;
   }
   __syncthreads();
-  const int bl = threadIdx.x % QS_BL;
-  const int ri = (threadIdx.x / QS_BL) % R;
-  const int slot = threadIdx.x / (QS_BL * R);
-  const long b0 = nblk * slot / NSLOT, b1 = nblk * (slot + 1) / NSLOT;
-  // this lane's two columns (2 bl, 2 bl + 1) of block 0 for its grid point
-  const T* tcol = tau + rb * rb_stride + (2 * bl * R + ri) * 8;
-  const int lo = bl * NBL * R + ri;  // lane offset inside an LDS row
-  int curI = -1;
-  T aI[8][NBL], acc[8][NBL];
-  // FP32 lanes have the registers to read the next block's columns while the
-  // current block is in use; FP64 lanes read each block when they reach it
-  constexpr bool PF = sizeof(T) == 4;
-  T nxt[2][8];
-  if (PF && b0 < b1) {
-    load8(nxt[0], tcol + b0 * 64 * R);
-    load8(nxt[1], tcol + b0 * 64 * R + 8 * R);
-  }
-#pragma unroll 1
-  for (long blk = b0; blk < b1; ++blk) {
-    const int2 bij = IJ[blk];
-    T own[2][8];
-    if (PF) {
+  const int bl = threadIdx.x % 4;
+  const int ri = (threadIdx.x / 4) % R;
+  const int slot = threadIdx.x / (4 * R);
+  const int b0 = (int)(nblk * slot / NS), b1 = (int)(nblk * (slot + 1) / NS);
+  const int lo = ri * NBT + bl * NBL;  // lane offset inside an LDS row
+  if (b0 < b1) {
+    // byte offsets of this lane's part of a block from the workgroup's run
+    constexpr unsigned BSTEP = 64 * R * sizeof(T), CSTEP = 8 * TC::COLS * R * sizeof(T);
+    const char* tb = reinterpret_cast<const char*>(tau + rb * rb_stride);
+    unsigned off = TC::lane_off(bl, ri, R) * sizeof(T) + b0 * BSTEP;
+    const int base = lo - row0 * rs;  // LDS index of band v: v * rs + base
+    T aI[8][NBL], acc[8][NBL];
+    int2 bij = IJ[b0];
+    __builtin_amdgcn_sched_barrier(0);
+    // a chunk of the next block is loaded as soon as the current block's has
+    // been used, so a whole block per lane stays in flight
+    // (the loads in the order of their use, here and below: a load out of
+    // order would make the loop's first wait one for all of them)
+    CH own[TC::N];
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) own[q][i] = nxt[q][i];
-      if (blk + 1 < b1) {
-        load8(nxt[0], tcol + (blk + 1) * 64 * R);
-        load8(nxt[1], tcol + (blk + 1) * 64 * R + 8 * R);
-      }
-    } else {
-      const T* tp = tcol + blk * 64 * R;
-      load8(own[0], tp);
-      load8(own[1], tp + 8 * R);
+    for (int k = 0; k < TC::N; ++k) {
+      own[k] = *reinterpret_cast<const CH*>(tb + off + k * CSTEP);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (bij.x != curI) {
-      if (curI >= 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int b = 0; b < NBL; ++b)
-            atomicAdd(&ys[(curI * 8 + i - row0) * RS + lo + b * R], (double)acc[i][b]);
-      }
-      curI = bij.x;
+    const char* ij = reinterpret_cast<const char*>(IJ);
+    int rowI = -1;
+    int run = RUNS ? slot * (VRUNS / NS) : 0, run_end = b0;
+    auto flush = [&]() {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int b = 0; b < NBL; ++b) {
-          aI[i][b] = as[(curI * 8 + i - row0) * RS + lo + b * R];
-          acc[i][b] = 0;
+        for (int b = 0; b < NBL; ++b) atomicAdd(&ys[rowI + i * rs + b], (double)acc[i][b]);
+    };
+#pragma unroll 1
+    for (int blk = b0; blk < b1; ++blk) {
+      const int rI = bij.x * 8 * rs + base, rowJ = bij.y * 8 * rs + base;
+      const bool more = blk + 1 < b1;
+      off += more ? BSTEP : 0;
+      bij = *reinterpret_cast<const int2*>(ij + (unsigned)(more ? blk + 1 : blk) * 8u);
+      bool fresh = rI != rowI;
+      if (RUNS && blk >= run_end) {  // a new run starts here
+        fresh = true;
+        do {
+          ++run;
+          run_end = (int)(nblk * run / VRUNS);
+        } while (run_end <= blk);
+      }
+      if (fresh) {
+        if (rowI >= 0) flush();
+        rowI = rI;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          lds_vec<T, NBL>(aI[i], as + rowI + i * rs);
+#pragma unroll
+          for (int b = 0; b < NBL; ++b) acc[i][b] = 0;
         }
+      }
+#pragma unroll
+      for (int k = 0; k < TC::N; ++k) {
+        const int j = k * TC::COLS;
+        qs_column<0, NBL>(own[k], acc, aI, as + rowJ + j * rs, ys + rowJ + j * rs);
+        if constexpr (TC::COLS == 2)
+          qs_column<1, NBL>(own[k], acc, aI, as + rowJ + (j + 1) * rs, ys + rowJ + (j + 1) * rs);
+        own[k] = *reinterpret_cast<const CH*>(tb + off + k * CSTEP);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    const int rowJ = bij.y * 8 - row0;
-    qs_column<0, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<1, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<2, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<3, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<4, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<5, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<6, R>(own, acc, aI, as, ys, rowJ, lo);
-    qs_column<7, R>(own, acc, aI, as, ys, rowJ, lo);
-  }
-  if (curI >= 0) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int b = 0; b < NBL; ++b)
-        atomicAdd(&ys[(curI * 8 + i - row0) * RS + lo + b * R], (double)acc[i][b]);
+    flush();
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n_el; e += NT) {
-    const int rr = e % R;
-    const int b = (e / R) % NBT;
-    const int vl = e / (R * NBT);
-    const int v = row0 + vl;
-    if (v < nv && b < nb) {
-      const long gi = ((long)b * nvh + (v >> 1)) * nr + r0 + rr;
-      const int li = vl * RS + b * R + rr;
-      T out = (T)ys[li];
-      if (FUSE) {
-        const long r = r0 + rr;
-        T z = -out;
-        if (with_v) z += V[r] * as[li];
-        if (vdrho) {
-          const T d = reinterpret_cast<const T*>(vdrho + (long)(b >> 1) * nr + r)[b & 1];
-          const T f = reinterpret_cast<const T*>(phir + (long)(v >> 1) * nr + r)[v & 1];
-          z += s * d * f;
-        }
-        out = z;
+  {
+    // the indices again from an opaque copy of the thread id: kept from the
+    // staging they would take registers the FP64 stream loop has not got
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    Walk w = walk(t);
+    const T vr = FUSE && with_v ? V[r0 + w.ri] : (T)0;
+    T sd = 0;
+    if (FUSE && vdrho && w.b < nb) {
+      const V2 dd = vdrho[(long)(w.b >> 1) * nr + r0 + w.ri];
+      sd = s * ((w.b & 1) ? dd.y : dd.x);
+    }
+    long gf = (long)(row0 / 2 + w.sp) * nr + r0 + w.ri;
+    for (int pl = w.sp; pl < w.vpair; pl += ST * PS, w.g += ST * w.gstep, gf += ST * w.gstep) {
+      V2 f[ST];
+      if (FUSE && vdrho) {
+#pragma unroll
+        for (int u = 0; u < ST; ++u) f[u] = phir[pl + u * PS < w.vpair ? gf + u * w.gstep : own0];
       }
-      reinterpret_cast<T*>(y + gi)[v & 1] = out;
+#pragma unroll
+      for (int u = 0; u < ST; ++u)
+        if (pl + u * PS < w.vpair) {
+          V2 out;
+          out.x = (T)ys[w.li];
+          out.y = (T)ys[w.li + rs];
+          if (FUSE) {
+            T z0 = -out.x, z1 = -out.y;
+            if (with_v) {
+              z0 += vr * as[w.li];
+              z1 += vr * as[w.li + rs];
+            }
+            if (vdrho) {
+              z0 += sd * f[u].x;
+              z1 += sd * f[u].y;
+            }
+            out.x = z0;
+            out.y = z1;
+          }
+          if (row0 + 2 * (pl + u * PS) + 1 >= nv) out.y = 0;
+          y[w.g + u * w.gstep] = out;
+          w.li += w.lstep;
+        }
     }
   }
 }
@@ -1333,17 +1301,20 @@ static int tau_store_impl(const G2* grids, const int2* blkIJ, long nblk, long nr
                           TD* dst, long dst_nblk, long dst_blk0, hipStream_t st) {
   const long n = (nr / R) * nblk * 64 * R;
   if (n <= 0) return BSE_OK;
-  if (tau_store_lds_on() && (R == 1 || R == 2)) {
+  if (tau_store_lds_on()) {
     const long nrb = nr / R;
     const long npg = (nrb + TS_P / R - 1) / (TS_P / R);
     const long nwg = npg * ((nblk + TS_NB - 1) / TS_NB);
     if (nwg > 0x7fffffffL) return fail(BSE_EINVAL, "tau store: %ld workgroups", nwg);
-    if (R == 2)
-      hipLaunchKernelGGL((k_tau_store_lds<G2, TD, 2>), dim3((unsigned)nwg), dim3(256), 0, st,
-                         grids, blkIJ, nblk, nr, dst, dst_nblk, dst_blk0);
-    else
-      hipLaunchKernelGGL((k_tau_store_lds<G2, TD, 1>), dim3((unsigned)nwg), dim3(256), 0, st,
-                         grids, blkIJ, nblk, nr, dst, dst_nblk, dst_blk0);
+#define GO(R_)                                                                                    \
+  if (R == R_)                                                                                    \
+    hipLaunchKernelGGL((k_tau_store_lds<G2, TD, R_>), dim3((unsigned)nwg), dim3(256), 0, st,      \
+                       grids, blkIJ, nblk, nr, dst, dst_nblk, dst_blk0)
+    GO(1);
+    GO(2);
+    GO(4);
+    GO(8);
+#undef GO
     CHECK_LAUNCH();
     return BSE_OK;
   }
@@ -1368,42 +1339,79 @@ int tau_store(const float2* grids, const int2* blkIJ, long nblk, long nr, int R,
   return tau_store_impl(grids, blkIJ, nblk, nr, R, dst, dst_nblk, dst_blk0, st);
 }
 
-size_t tau_stream_lds(int nv, int R, size_t elem, int bl) {
-  (void)bl;  // every variant stages the same LDS rows
-  const int nv8 = (nv + 7) / 8 * 8;
-  return (elem + sizeof(double)) * (size_t)nv8 * (NBT * R + SPAD);
+// values of an LDS row of the stream kernels (one band, R points, nbt
+// vectors): padded by two values when that still fits
+static int tau_stream_row(int nv8, int R, int nbt, size_t elem, size_t max_lds) {
+  const int row = nbt * R, pad = 2;
+  return (elem + sizeof(double)) * (size_t)nv8 * (row + pad) <= max_lds ? row + pad : row;
 }
 
-template <int R, bool F, typename T>
-static void launch_stream_qs(long nrb, size_t shm, hipStream_t st, const T* tau, long stride,
-                             long nblk, const int2* blkIJ, const typename vec2_of<T>::type* a,
-                             typename vec2_of<T>::type* y, int nb, int nv, long nr, int row0,
-                             int nrows, int accumulate, const T* V,
-                             const typename vec2_of<T>::type* vdrho,
-                             const typename vec2_of<T>::type* phir, T s, int with_v) {
-  hipLaunchKernelGGL((k_tau_stream_qs<R, F, T>), dim3((unsigned)nrb), dim3(NSLOT * R * QS_BL),
-                     shm, st, tau, stride, nblk, blkIJ, a, y, nb, nv, (nv + 1) / 2, nr, row0,
-                     nrows, accumulate, V, vdrho, phir, s, with_v);
+size_t tau_stream_lds(int nv, int R, size_t elem) {
+  return (elem + sizeof(double)) * (size_t)((nv + 7) / 8 * 8) * (8 * R + 1);
 }
 
-template <int R, int BL, bool F, typename T>
-static void launch_stream(long nrb, size_t shm, hipStream_t st, const T* tau, long stride,
-                          long nblk, const int2* blkIJ, const typename vec2_of<T>::type* a,
-                          typename vec2_of<T>::type* y, int nb, int nv, long nr, int row0,
-                          int nrows, int accumulate, const T* V,
-                          const typename vec2_of<T>::type* vdrho,
-                          const typename vec2_of<T>::type* phir, T s, int with_v) {
-  hipLaunchKernelGGL((k_tau_stream<R, BL, F, T>), dim3((unsigned)nrb), dim3(NSLOT * R * BL), shm,
-                     st, tau, stride, nblk, blkIJ, a, y, nb, nv, (nv + 1) / 2, nr, row0, nrows,
-                     accumulate, V, vdrho, phir, s, with_v);
+// Grid points per workgroup.  More points give longer contiguous pieces of
+// a(r), z(r) and tau and fewer row blocks per wave (fewer LDS bank
+// conflicts), as long as the LDS they take leaves 12 to 16 waves per CU:
+// 8 points up to 32 KB, 4 points up to the whole LDS in FP64 (one workgroup
+// of 16 waves) and half of it in FP32, whose shorter rows stay ahead with two
+// workgroups, else 2.  Measured, ms per launch at 2 / 4 / 8 points with the
+// best workgroup size of each (8 vectors unless noted): FP64 24^3 N_v 16
+// (5 vectors) 0.032 / 0.021 / 0.017, 64^3 N_v 80 2.69 / 2.27 / 2.34,
+// 32^3 N_v 107 (5 vectors) 0.469 / 0.456 / 0.475, 64^3 N_v 200
+// 11.36 / 10.48 / -, 60^3 N_v 300 19.5 / 18.2 / -; FP32 32^3 N_v 107
+// 0.295 / 0.272 / 0.366, 48^3 N_v 180 2.16 / 2.17 / 2.34, 60^3 N_v 300
+// 10.2 / 10.8 / -.
+int tau_stream_points(int nv, long nr, size_t elem, size_t max_lds) {
+  if (nr % 8 == 0 && tau_stream_lds(nv, 8, elem) <= 32768) return 8;
+  if (nr % 4 == 0 && tau_stream_lds(nv, 4, elem) <= (elem == 8 ? max_lds : max_lds / 2)) return 4;
+  return tau_stream_lds(nv, 2, elem) <= max_lds ? 2 : 1;
+}
+
+template <typename T>
+struct StreamArgs {
+  using V2 = typename vec2_of<T>::type;
+  const T* tau;
+  long stride, nblk;
+  const int2* blkIJ;
+  const V2* a;
+  V2* y;
+  int nb, nv;
+  long nr;
+  int row0, rows, rs, accumulate;
+  const T* V;
+  const V2 *vdrho, *phir;
+  T s;
+  int with_v;
+  bool fuse;
+};
+
+// the compiled (R, threads) pairs: every pair the two rules can choose
+#define BSEX_STREAM_SIZES(X) X(1, 512) X(2, 256) X(2, 512) X(2, 1024) X(4, 256) X(4, 512) X(4, 1024) X(8, 256)
+
+template <int R, int NT, int NBL, bool F, typename T>
+static void launch_stream(const StreamArgs<T>& g, size_t shm, hipStream_t st) {
+  hipLaunchKernelGGL((k_tau_stream_qs<R, NT, NBL, F, T>), dim3((unsigned)(g.nr / R)), dim3(NT), shm,
+                     st, g.tau, g.stride, g.nblk, g.blkIJ, g.a, g.y, g.nb, g.nv, (g.nv + 1) / 2,
+                     g.nr, g.row0, g.rows, g.rs, g.accumulate, g.V, g.vdrho, g.phir, g.s, g.with_v);
+}
+
+template <int R, int NT, typename T>
+static void launch_stream_size(const StreamArgs<T>& g, size_t shm, hipStream_t st) {
+  if (g.nb > 4)
+    g.fuse ? launch_stream<R, NT, 2, true, T>(g, shm, st)
+           : launch_stream<R, NT, 2, false, T>(g, shm, st);
+  else
+    g.fuse ? launch_stream<R, NT, 1, true, T>(g, shm, st)
+           : launch_stream<R, NT, 1, false, T>(g, shm, st);
 }
 
 template <typename T, typename FA>
 static int tau_stream_impl(const T* tau, long buf_nblk, long nblk, const int2* blkIJ, int R,
                            const typename vec2_of<T>::type* a, typename vec2_of<T>::type* y,
                            int nb, int nv, long nr, int accumulate, size_t max_lds,
-                           hipStream_t st, const FA* fuse, int bl, int row0, int rows) {
-  if (nb > NBT) return fail(BSE_EINVAL, "tau_stream: at most %d vectors per call", NBT);
+                           hipStream_t st, const FA* fuse, int row0, int rows) {
+  if (nb > 8) return fail(BSE_EINVAL, "tau_stream: at most 8 vectors per call");
   if (nr % R) return fail(BSE_EINVAL, "tau_stream: grid size not a multiple of %d", R);
   const int nv8 = (nv + 7) / 8 * 8;
   if (rows <= 0) {
@@ -1413,85 +1421,81 @@ static int tau_stream_impl(const T* tau, long buf_nblk, long nblk, const int2* b
   if (row0 < 0 || row0 % 8 || rows % 8 || row0 + rows > nv8)
     return fail(BSE_EINVAL, "tau_stream: band rows %d..%d outside 0..%d", row0, row0 + rows, nv8);
   if (fuse && rows != nv8) return fail(BSE_EINVAL, "tau_stream: the fused epilogue needs every band");
-  const size_t shm = tau_stream_lds(rows, R, sizeof(T), bl);
+  if (nr / R > 0x7fffffffL) return fail(BSE_EINVAL, "tau_stream: grid too large");
+  // byte offsets inside a workgroup's run and the block index are 32-bit
+  if (nblk > 0x7fffffffL / (long)(64 * R * sizeof(T)))
+    return fail(BSE_EINVAL, "tau_stream: %ld blocks in one launch", nblk);
+  // up to 4 vectors: one per lane of a quad instead of two, half the LDS
+  // (64^3 N_v 200, one vector: 7.2 ms against 8.6 with 8 vector slots)
+  const int nbt = nb > 4 ? 8 : 4;
+  const int rs = tau_stream_row(rows, R, nbt, sizeof(T), max_lds);
+  const size_t shm = (sizeof(T) + sizeof(double)) * (size_t)rows * rs;
   if (shm > max_lds) return fail(BSE_EINVAL, "tau_stream: %zu bytes of LDS exceed %zu", shm, max_lds);
-  const long nrb = nr / R;
-  if (nrb > 0x7fffffffL) return fail(BSE_EINVAL, "tau_stream: grid too large");
-  const long stride = buf_nblk * 64 * R;
-  const T* V = fuse ? fuse->V : nullptr;
-  const typename vec2_of<T>::type* vd = fuse ? fuse->vdrho : nullptr;
-  const typename vec2_of<T>::type* ph = fuse ? fuse->phir : nullptr;
-  const T sf = fuse ? (T)fuse->s : (T)0;
-  const int wv = fuse ? fuse->with_v : 0;
-#define GO(R_, BL_)                                                                              \
-  do {                                                                                           \
-    if (fuse)                                                                                    \
-      launch_stream<R_, BL_, true, T>(nrb, shm, st, tau, stride, nblk, blkIJ, a, y, nb, nv, nr,   \
-                                      row0, rows, accumulate, V, vd, ph, sf, wv);                \
-    else                                                                                         \
-      launch_stream<R_, BL_, false, T>(nrb, shm, st, tau, stride, nblk, blkIJ, a, y, nb, nv, nr,  \
-                                       row0, rows, accumulate, V, vd, ph, sf, wv);               \
-  } while (0)
-#define GO_QS(R_)                                                                                \
-  do {                                                                                           \
-    if (fuse)                                                                                    \
-      launch_stream_qs<R_, true, T>(nrb, shm, st, tau, stride, nblk, blkIJ, a, y, nb, nv, nr,     \
-                                    row0, rows, accumulate, V, vd, ph, sf, wv);                  \
-    else                                                                                         \
-      launch_stream_qs<R_, false, T>(nrb, shm, st, tau, stride, nblk, blkIJ, a, y, nb, nv, nr,    \
-                                     row0, rows, accumulate, V, vd, ph, sf, wv);                 \
-  } while (0)
-  if (R == 2 && bl == 1)
-    GO_QS(2);
-  else if (R == 1 && bl == 1)
-    GO_QS(1);
-  else if (R == 2 && bl == 4)
-    GO(2, 4);
-  else if (R == 2 && bl == 2)
-    GO(2, 2);
-  else if (R == 1 && bl == 4)
-    GO(1, 4);
-  else if (R == 1 && bl == 2)
-    GO(1, 2);
-  else
-    return fail(BSE_EINVAL, "tau_stream: R = %d, BL = %d unsupported", R, bl);
+  // Threads: the fewest that keep 12 waves on a CU (the registers allow 16)
+  // with the workgroups its LDS holds; fewer slots leave each a longer run of
+  // blocks, and several workgroups overlap one's staging with another's
+  // stream.  FP64 64^3 N_v 80, 3 workgroups: 2.27 / 2.37 / 2.92 ms with 256 /
+  // 512 / 1024 threads; 72^3 N_v 432, 1 workgroup: 67.4 / 60.4 / 59.1 ms.
+  const size_t per_cu = std::max<size_t>(1, max_lds / std::max<size_t>(shm, 1));
+  int nt = 256;
+  while (nt < 1024 && nt * per_cu < 768) nt *= 2;
+  if (R == 1) nt = 512;
+  if (R == 8) nt = 256;  // at most 32 KB: five workgroups and more
+  StreamArgs<T> g{tau, buf_nblk * 64 * R, nblk, blkIJ, a, y, nb, nv, nr, row0, rows, rs, accumulate,
+                  fuse ? fuse->V : nullptr, fuse ? fuse->vdrho : nullptr,
+                  fuse ? fuse->phir : nullptr, fuse ? (T)fuse->s : (T)0, fuse ? fuse->with_v : 0,
+                  fuse != nullptr};
+#define GO(R_, NT_)                            \
+  if (R == R_ && nt == NT_) {                  \
+    launch_stream_size<R_, NT_, T>(g, shm, st); \
+    CHECK_LAUNCH();                            \
+    return BSE_OK;                             \
+  }
+  BSEX_STREAM_SIZES(GO)
 #undef GO
-#undef GO_QS
-  CHECK_LAUNCH();
+  return fail(BSE_EINVAL, "tau_stream: R = %d unsupported", R);
+}
+
+template <int R, int NT, int NBL, bool F, typename T>
+static int stream_lds_limit(int bytes) {
+  BSE_HIP(hipFuncSetAttribute((const void*)k_tau_stream_qs<R, NT, NBL, F, T>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  return BSE_OK;
+}
+
+template <int R, int NT, typename T>
+static int stream_lds_limits(int bytes) {
+  BSE_TRY((stream_lds_limit<R, NT, 1, false, T>(bytes)));
+  BSE_TRY((stream_lds_limit<R, NT, 1, true, T>(bytes)));
+  BSE_TRY((stream_lds_limit<R, NT, 2, false, T>(bytes)));
+  return stream_lds_limit<R, NT, 2, true, T>(bytes);
+}
+
+int tau_stream_set_lds_limit(int R, size_t elem, size_t bytes) {
+#define GO(R_, NT_)                                                                   \
+  if (R == R_) {                                                                      \
+    if (elem == 8)                                                                    \
+      BSE_TRY((stream_lds_limits<R_, NT_, double>((int)bytes)));                      \
+    else                                                                              \
+      BSE_TRY((stream_lds_limits<R_, NT_, float>((int)bytes)));                       \
+  }
+  BSEX_STREAM_SIZES(GO)
+#undef GO
   return BSE_OK;
 }
 
 int tau_stream(const double* tau, long buf_nblk, long nblk, const int2* blkIJ, int R,
                const double2* a, double2* y, int nb, int nv, long nr, int accumulate,
-               size_t max_lds, hipStream_t st, const FuseArgs* fuse, int bl, int row0, int rows) {
+               size_t max_lds, hipStream_t st, const FuseArgs* fuse, int row0, int rows) {
   return tau_stream_impl(tau, buf_nblk, nblk, blkIJ, R, a, y, nb, nv, nr, accumulate, max_lds, st,
-                         fuse, bl, row0, rows);
+                         fuse, row0, rows);
 }
 
 int tau_stream(const float* tau, long buf_nblk, long nblk, const int2* blkIJ, int R,
                const float2* a, float2* y, int nb, int nv, long nr, int accumulate,
-               size_t max_lds, hipStream_t st, const FuseArgsF* fuse, int bl, int row0, int rows) {
+               size_t max_lds, hipStream_t st, const FuseArgsF* fuse, int row0, int rows) {
   return tau_stream_impl(tau, buf_nblk, nblk, blkIJ, R, a, y, nb, nv, nr, accumulate, max_lds, st,
-                         fuse, bl, row0, rows);
-}
-
-int tau_stream_set_lds_limit(size_t bytes) {
-  const void* fns[] = {
-      (const void*)k_tau_stream<2, 4, false, double>, (const void*)k_tau_stream<2, 2, false, double>,
-      (const void*)k_tau_stream<1, 4, false, double>, (const void*)k_tau_stream<1, 2, false, double>,
-      (const void*)k_tau_stream<2, 4, true, double>,  (const void*)k_tau_stream<2, 2, true, double>,
-      (const void*)k_tau_stream<1, 4, true, double>,  (const void*)k_tau_stream<1, 2, true, double>,
-      (const void*)k_tau_stream<2, 4, false, float>,  (const void*)k_tau_stream<2, 2, false, float>,
-      (const void*)k_tau_stream<1, 4, false, float>,  (const void*)k_tau_stream<1, 2, false, float>,
-      (const void*)k_tau_stream<2, 4, true, float>,   (const void*)k_tau_stream<2, 2, true, float>,
-      (const void*)k_tau_stream<1, 4, true, float>,   (const void*)k_tau_stream<1, 2, true, float>,
-      (const void*)k_tau_stream_qs<2, false, double>, (const void*)k_tau_stream_qs<2, true, double>,
-      (const void*)k_tau_stream_qs<1, false, double>, (const void*)k_tau_stream_qs<1, true, double>,
-      (const void*)k_tau_stream_qs<2, false, float>,  (const void*)k_tau_stream_qs<2, true, float>,
-      (const void*)k_tau_stream_qs<1, false, float>,  (const void*)k_tau_stream_qs<1, true, float>};
-  for (const void* f : fns)
-    BSE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return BSE_OK;
+                         fuse, row0, rows);
 }
 
 int site_potential(const double* xyz, const double* depth, const double* width, int nsites,

@@ -458,7 +458,7 @@ static int tau_contract(bse_ctx* c, const double2* orbr, const double2* a, doubl
   if (use_cache && c->nblk_cached > 0) {
     PhaseScope ps(c, PH_TAU_STREAM);
     BSE_TRY(tau_stream(c->tau_cache, c->nblk_cached, c->nblk_cached, c->blkIJ, c->R, a, y, nb,
-                       c->nv, nr, 0, c->max_lds, c->st, fuse, c->tau_bl));
+                       c->nv, nr, 0, c->max_lds, c->st, fuse));
     first = 0;
     start = c->nblk_cached;
   }
@@ -472,7 +472,7 @@ static int tau_contract(bse_ctx* c, const double2* orbr, const double2* a, doubl
     int row0 = 0, rows = 0;  // the first launch writes every band of y
     if (!first) tile_rows(c, gb0, nt, &row0, &rows);
     BSE_TRY(tau_stream(c->rebuild_buf, nt, nt, c->blkIJ + gb0, c->R, a, y, nb, c->nv, nr,
-                       first ? 0 : 1, c->max_lds, c->st, nullptr, c->tau_bl, row0, rows));
+                       first ? 0 : 1, c->max_lds, c->st, nullptr, row0, rows));
     first = 0;
   }
   return BSE_OK;
@@ -727,7 +727,7 @@ int kernel_part(bse_ctx* c, const double2* agrid, double* Kt) {
     {
       PhaseScope ps(c, PH_TAU_STREAM);
       BSE_TRY(tau_stream(c->tau_f, c->nblk, c->nblk, c->blkIJ, c->Rf, af, yf, 1, c->nv, nr, 0,
-                         c->max_lds, c->st, nullptr, c->tau_bl));
+                         c->max_lds, c->st));
     }
     BSE_TRY(to_f64(reinterpret_cast<const float*>(yf), reinterpret_cast<double*>(y), 2 * ng,
                    c->st));
@@ -765,7 +765,7 @@ int sigma_phi(bse_ctx* c, const double2* agrid, double2* y) {
     int row0 = 0, rows = 0;  // the first launch writes every band of y
     if (gb0 > 0) tile_rows(c, gb0, nt, &row0, &rows);
     BSE_TRY(tau_stream(buf, nt, nt, c->blkIJ + gb0, c->Rf, c->phik_f, yf, 1, c->nv, nr,
-                       gb0 == 0 ? 0 : 1, c->max_lds, c->st, nullptr, c->tau_bl, row0, rows));
+                       gb0 == 0 ? 0 : 1, c->max_lds, c->st, nullptr, row0, rows));
   }
   return to_f64(reinterpret_cast<const float*>(yf), reinterpret_cast<double*>(y), 2 * ng, c->st);
 }
@@ -837,7 +837,7 @@ int apply_chunk_mixed(bse_ctx* c, int nb, const double* X, double* Y) {
     PhaseScope ps(c, PH_TAU_STREAM);
     FuseArgsF f{c->Vr_f, vdrho, c->phik_f, c->spin, with_v};
     BSE_TRY(tau_stream(c->tau_f, c->nblk, c->nblk, c->blkIJ, c->Rf, c->agrid_f, c->agrid_f, nb,
-                       c->nv, nr, 0, c->max_lds, c->st, &f, c->tau_bl));
+                       c->nv, nr, 0, c->max_lds, c->st, &f));
   } else {
     PhaseScope ps(c, PH_COMBINE);
     BSE_TRY(combine(c->agrid_f, c->phik_f, c->Vr_f, vdrho, nullptr, c->agrid_f, c->nv, nb, nr,
