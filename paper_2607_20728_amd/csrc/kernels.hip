@@ -681,8 +681,14 @@ __global__ __launch_bounds__(NT, 4) void k_tau_stream_qs(
             out.x = z0;
             out.y = z1;
           }
-          if (row0 + 2 * (pl + u * PS) + 1 >= nv) out.y = 0;
-          y[w.g + u * w.gstep] = out;
+          // an odd count leaves the last pair one band: the fused form keeps
+          // what its other half holds, the sums are defined for both halves
+          const bool two = row0 + 2 * (pl + u * PS) + 1 < nv;
+          if (!two) out.y = 0;
+          if (two || !FUSE)
+            y[w.g + u * w.gstep] = out;
+          else
+            y[w.g + u * w.gstep].x = out.x;
           w.li += w.lstep;
         }
     }
