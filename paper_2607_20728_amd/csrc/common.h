@@ -147,6 +147,25 @@ int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const double2* orb, 
 int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const float2* orb, int nv,
                     const int2* IJ, long nblk, float2* data, const float* f, float s,
                     float2* compact, hipStream_t st);
+// Where a W build leaves its blocks: the tau layout of 2^sh64 points in FP64
+// and / or of 2^sh32 points in FP32 (d64 or d32 may be NULL), buffers of
+// nblk* blocks per r-block, from block blk*.
+struct TauOut {
+  double* d64 = nullptr;
+  long nblk64 = 0, blk64 = 0;
+  int sh64 = 0;
+  float* d32 = nullptr;
+  long nblk32 = 0, blk32 = 0;
+  int sh32 = 0;
+};
+// Inverse 3-D FFT of the pair grids of nblk blocks (32 grids each), written
+// by its last pass into the tau layout instead of the grids (which are
+// overwritten).  Needs a direct-access pass for the axis-1 length, as
+// fwd_pairs_supported tells.
+int fft3d_inv_store(const FftPlan& p, double2* data, const int2* IJ, long nblk, const TauOut& o,
+                    hipStream_t st);
+int fft3d_inv_store(const FftPlan& p, float2* data, const int2* IJ, long nblk, const TauOut& o,
+                    hipStream_t st);
 // ... and with grid q < nm formed as M[q] times the real field x
 // (component xc of the packed grid x2), the pair products of the
 // exchange-like terms

@@ -205,6 +205,14 @@ int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const float2* orb, i
                     float2* compact, hipStream_t st) {
   return f32::fft3d_fwd_pairs(p, sp, orb, nv, IJ, nblk, data, f, s, compact, st);
 }
+int fft3d_inv_store(const FftPlan& p, double2* data, const int2* IJ, long nblk, const TauOut& o,
+                    hipStream_t st) {
+  return f64::fft3d_inv_store(p, data, IJ, nblk, o, st);
+}
+int fft3d_inv_store(const FftPlan& p, float2* data, const int2* IJ, long nblk, const TauOut& o,
+                    hipStream_t st) {
+  return f32::fft3d_inv_store(p, data, IJ, nblk, o, st);
+}
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
                    int nset, double2* grid, hipStream_t st) {
   return f64::sphere_to_grid(p, sp, omega, X, nv, nset, grid, st);

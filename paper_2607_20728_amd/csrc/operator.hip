@@ -363,6 +363,22 @@ int tau_build_range(bse_ctx* c, const double2* orbr, long gb0, long nblk, double
   else if (!fused)  // a fill kernel, not a memset: this may run inside a captured graph
     BSE_TRY(zero_fill(reinterpret_cast<double*>(c->tile_grids), 2 * ng * nr, c->st));
   if (pdep) BSE_TRY(scatter_sets(m64, c->tile_F, 64, (int)nblk, c->tile_grids, 1, c->st));
+  if (fwd_pairs_supported(c->fft, false)) {
+    TauOut o;
+    if (dst) {
+      o.d64 = dst;
+      o.nblk64 = dst_nblk;
+      o.blk64 = dst_blk0;
+      o.sh64 = __builtin_ctz(c->R);
+    }
+    if (dstf) {
+      o.d32 = dstf;
+      o.nblk32 = c->nblk;
+      o.blk32 = gb0;
+      o.sh32 = __builtin_ctz(c->Rf);
+    }
+    return fft3d_inv_store(c->fft, c->tile_grids, c->blkIJ + gb0, nblk, o, c->st);
+  }
   BSE_TRY(fft3d(c->fft, c->tile_grids, ng, +1, c->st));
   if (dstf)
     BSE_TRY(tau_store(c->tile_grids, c->blkIJ + gb0, nblk, nr, c->Rf, dstf, c->nblk, gb0, c->st));
@@ -430,6 +446,14 @@ int tau_build_range_f(bse_ctx* c, const float2* orbr, long gb0, long nblk, float
     BSE_TRY(scatter_sets(m64, tf, 64, (int)nblk, tg, 1, c->st));
   else if (pdep)
     BSE_TRY(scatter_sets(m64, c->tile_F, 64, (int)nblk, tg, 1, c->st));
+  if (fwd_pairs_supported(c->fft, true)) {
+    TauOut o;
+    o.d32 = dst;
+    o.nblk32 = dst_nblk;
+    o.blk32 = dst_blk0;
+    o.sh32 = __builtin_ctz(c->Rf);
+    return fft3d_inv_store(c->fft, tg, c->blkIJ + gb0, nblk, o, c->st);
+  }
   BSE_TRY(fft3d(c->fft, tg, ng, +1, c->st));
   return tau_store(tg, c->blkIJ + gb0, nblk, nr, c->Rf, dst, dst_nblk, dst_blk0, c->st);
 }

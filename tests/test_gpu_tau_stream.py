@@ -27,7 +27,10 @@ SHAPES = [((12, 12, 12), 6.0, 3),     # 8 points, one block
           ((12, 12, 12), 6.0, 105),   # 4 points, 512 threads
           ((12, 12, 12), 6.0, 160),   # 4 points, 1024 threads
           ((9, 10, 15), 4.0, 31),     # 2 points: the grid is no multiple of 4
-          ((16, 16, 16), 12.0, 610)]  # 1 point: two do not fit the LDS
+          ((16, 16, 16), 12.0, 610),  # 1 point: two do not fit the LDS
+          # lengths of the storing axis-1 transform: three passes (two of its
+          # buffers), its shortest tiles, and a last tile that is not full
+          ((30, 12, 12), 6.0, 9), ((80, 9, 10), 4.0, 17), ((128, 12, 12), 6.0, 9)]
 
 
 def _system(grid, ecut, nv):
