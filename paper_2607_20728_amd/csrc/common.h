@@ -160,12 +160,42 @@ struct TauOut {
 };
 // Inverse 3-D FFT of the pair grids of nblk blocks (32 grids each), written
 // by its last pass into the tau layout instead of the grids (which are
-// overwritten).  Needs a direct-access pass for the axis-1 length, as
+// overwritten); planes_done: the plane transforms were made by
+// fft3d_w_planes.  Needs a direct-access pass for the axis-1 length, as
 // fwd_pairs_supported tells.
 int fft3d_inv_store(const FftPlan& p, double2* data, const int2* IJ, long nblk, const TauOut& o,
-                    hipStream_t st);
+                    bool planes_done, hipStream_t st);
 int fft3d_inv_store(const FftPlan& p, float2* data, const int2* IJ, long nblk, const TauOut& o,
-                    hipStream_t st);
+                    bool planes_done, hipStream_t st);
+// A W solve in three passes over the grids, where the plane has a kernel
+// (w_planes_supported): an axis-1 pass (fft3d_axis, or pairs_axis /
+// times_axis, which form the grids in it), the plane part below, and the
+// inverse axis-1 pass (fft3d_axis or fft3d_inv_store).  The plane part
+// leaves each grid as the inverse plane transform of
+//   (forward plane transform) * f(G) s  (zero when f is NULL)
+//   + the sphere coefficients X or Xf, rows 2g and 2g + 1 for grid g < batch
+//     (nrow rows; both NULL for none),
+// and planes_to_compact gives the forward transform's sphere entries, which
+// the PDEP projection makes X from, ahead of it.
+bool w_planes_supported(const FftPlan& p, bool f32);
+int fft3d_axis(const FftPlan& p, double2* data, long batch, int dir, hipStream_t st);
+int fft3d_axis(const FftPlan& p, float2* data, long batch, int dir, hipStream_t st);
+int pairs_axis(const FftPlan& p, const double2* orb, int nv, const int2* IJ, long nblk,
+               double2* data, hipStream_t st);
+int pairs_axis(const FftPlan& p, const float2* orb, int nv, const int2* IJ, long nblk,
+               float2* data, hipStream_t st);
+int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc,
+               double2* data, hipStream_t st);
+int planes_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,
+                      double2* compact, hipStream_t st);
+int planes_to_compact(const FftPlan& p, const SpherePlan& sp, float2* grid, long batch,
+                      float2* compact, hipStream_t st);
+int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, double2* data, long batch,
+                   const double* f, double s, const double* X, const float* Xf, long nrow,
+                   double omega, hipStream_t st);
+int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, float2* data, long batch,
+                   const float* f, float s, const double* X, const float* Xf, long nrow,
+                   double omega, hipStream_t st);
 // ... and with grid q < nm formed as M[q] times the real field x
 // (component xc of the packed grid x2), the pair products of the
 // exchange-like terms

@@ -181,6 +181,8 @@ int to_grid(bse_ctx* c, const double* X, int nvs, int nset, double2* grids);
 // plus (T + shift - eps_v) A when A is given
 int from_grid(bse_ctx* c, double2* grids, int nvs, int nset, const double* A, const double* eps,
               double shift, double* Y);
+// v_c * g on ng complex grids, in place (scale: 1/N_r times a factor)
+int poisson(bse_ctx* c, double2* g, long ng, double scale);
 int kernel_part(bse_ctx* c, const double2* agrid, double* Kt);
 int sigma_phi(bse_ctx* c, const double2* agrid, double2* y);
 int orth_block(bse_ctx* c, const double* V, long m, double* W, long k, long len, double* tmp,

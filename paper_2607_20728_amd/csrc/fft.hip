@@ -206,12 +206,51 @@ int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const float2* orb, i
   return f32::fft3d_fwd_pairs(p, sp, orb, nv, IJ, nblk, data, f, s, compact, st);
 }
 int fft3d_inv_store(const FftPlan& p, double2* data, const int2* IJ, long nblk, const TauOut& o,
-                    hipStream_t st) {
-  return f64::fft3d_inv_store(p, data, IJ, nblk, o, st);
+                    bool planes_done, hipStream_t st) {
+  return f64::fft3d_inv_store(p, data, IJ, nblk, o, planes_done, st);
 }
 int fft3d_inv_store(const FftPlan& p, float2* data, const int2* IJ, long nblk, const TauOut& o,
-                    hipStream_t st) {
-  return f32::fft3d_inv_store(p, data, IJ, nblk, o, st);
+                    bool planes_done, hipStream_t st) {
+  return f32::fft3d_inv_store(p, data, IJ, nblk, o, planes_done, st);
+}
+bool w_planes_supported(const FftPlan& p, bool f32) {
+  return f32 ? f32::w_planes_supported(p) : f64::w_planes_supported(p);
+}
+int fft3d_axis(const FftPlan& p, double2* data, long batch, int dir, hipStream_t st) {
+  return f64::fft3d_axis(p, data, batch, dir, st);
+}
+int fft3d_axis(const FftPlan& p, float2* data, long batch, int dir, hipStream_t st) {
+  return f32::fft3d_axis(p, data, batch, dir, st);
+}
+int pairs_axis(const FftPlan& p, const double2* orb, int nv, const int2* IJ, long nblk, double2* data,
+               hipStream_t st) {
+  return f64::pairs_axis(p, orb, nv, IJ, nblk, data, st);
+}
+int pairs_axis(const FftPlan& p, const float2* orb, int nv, const int2* IJ, long nblk, float2* data,
+               hipStream_t st) {
+  return f32::pairs_axis(p, orb, nv, IJ, nblk, data, st);
+}
+int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc,
+               double2* data, hipStream_t st) {
+  return f64::times_axis(p, M, nm, x2, xc, data, st);
+}
+int planes_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,
+                      double2* compact, hipStream_t st) {
+  return f64::planes_to_compact(p, sp, grid, batch, compact, st);
+}
+int planes_to_compact(const FftPlan& p, const SpherePlan& sp, float2* grid, long batch,
+                      float2* compact, hipStream_t st) {
+  return f32::planes_to_compact(p, sp, grid, batch, compact, st);
+}
+int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, double2* data, long batch, const double* f,
+                   double s, const double* X, const float* Xf, long nrow, double omega,
+                   hipStream_t st) {
+  return f64::fft3d_w_planes(p, sp, data, batch, f, s, X, Xf, nrow, omega, st);
+}
+int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, float2* data, long batch, const float* f,
+                   float s, const double* X, const float* Xf, long nrow, double omega,
+                   hipStream_t st) {
+  return f32::fft3d_w_planes(p, sp, data, batch, f, s, X, Xf, nrow, omega, st);
 }
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
                    int nset, double2* grid, hipStream_t st) {

@@ -443,8 +443,6 @@ __global__ __launch_bounds__(kPlaneThreads) void k_fft_plane_ct(cplx* data, Plan
   if (OUT == 0) {
 #pragma unroll 4
     for (int e = threadIdx.x; e < NP2; e += NT) gp[e] = P[e];
-  } else if (OUT == 2) {
-    plane_store_w(P, gp, pa, g, i1, NP2, NT);
   } else {
     cplx* cg = pa.compact + g * (long)pa.nent;
     for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT)
@@ -694,6 +692,190 @@ __global__ __launch_bounds__(kPlaneThreads) void k_sphere_fwd_whole(cplx* data, 
   cplx* cg = pa.compact + g * (long)pa.nent;
   for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT)
     cg[e] = P[pa.ent_pos[e]];
+}
+
+// ---------------------------------------------------------------------------
+// The plane part of a W solve in one visit: forward transform of both
+// in-plane axes, times f(G) s, plus the PDEP part on the sphere's modes
+// (rows of coefficients X, as k_scatter adds them), and the inverse
+// transform of both axes.  The plane stays in LDS, every pass in place: all
+// butterflies of a pass are read into registers before any is written.  Rows
+// are padded to an odd length, so lanes on neighbouring rows (row passes)
+// and on neighbouring columns (column passes) fall into different banks.
+// Bound by its LDS passes and barriers where one workgroup fills a CU, near
+// HBM (one read and one write of the grids) where two or more fit.  With the
+// forward and inverse transforms as kernels of their own (through scratch
+// lines in LDS, the grids written and read between them) and a scatter, FP64
+// 64^3, 10,400 grids: 31.5 + 5.4 + 25.2 ms, now 11.8 for the sphere entries
+// and 23.9 here (3.6 TB/s); 72^3, 8,544 grids: 35.9 + 3.4 + 30.0, now 10.2 +
+// 39.2 (2.6 TB/s, one workgroup per CU); FP32 48 x 120: 13.9 + 5.7 + 12.2,
+// now 11.8 + 16.3.
+// ---------------------------------------------------------------------------
+template <int N2, int N3>
+constexpr int wp_rs() {
+  return N3 % 2 ? N3 : N3 + 1;
+}
+template <int N2, int N3>
+constexpr size_t wp_lds() {
+  return sizeof(cplx) * (size_t)N2 * wp_rs<N2, N3>();
+}
+// threads: one butterfly each in the passes of radix 4 and more
+template <int N2, int N3>
+constexpr int wp_nt() {
+  int t = 64;
+  const Fac a = factor(N2), b = factor(N3);
+  for (int p = 0; p < a.n; ++p)
+    if (a.r[p] >= 4 && N2 / a.r[p] * N3 > t) t = N2 / a.r[p] * N3;
+  for (int p = 0; p < b.n; ++p)
+    if (b.r[p] >= 4 && N3 / b.r[p] * N2 > t) t = N3 / b.r[p] * N2;
+  t = (t + 63) / 64 * 64;
+  return t > 768 ? 768 : t;
+}
+
+// one Stockham pass of radix R over NL lines, in place: aux(k, l) is read
+// early for every output and handed to put(k, l, value, aux)
+template <int R, int DIR, int N, int NS, int NL, int NT, class GET, class AUX, class PUT>
+__device__ __forceinline__ void pass_inplace(GET get, AUX aux, PUT put,
+                                             const cplx* __restrict__ tw) {
+  constexpr int NQ = N / R, TS = N / (NS * R);
+  constexpr int TASKS = NQ * NL, MT = (TASKS + NT - 1) / NT;
+  using A = decltype(aux(0, 0));
+  cplx v[MT][R];
+  A ax[MT][R];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int u = threadIdx.x + t * NT;
+    if (TASKS % NT == 0 || u < TASKS) {
+      const int l = u % NL, j = u / NL, k = j % NS;
+      const int base = (j / NS) * NS * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) ax[t][r] = aux(base + r * NS, l);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        cplx x = get(j + r * NQ, l);
+        if (r > 0 && NS > 1) {
+          cplx w = tw[k * r * TS];
+          if (DIR > 0) w.y = -w.y;
+          x = cmul(x, w);
+        }
+        v[t][r] = x;
+      }
+      if (R == 2) dft2<DIR>(v[t]);
+      if (R == 3) dft3<DIR>(v[t]);
+      if (R == 4) dft4<DIR>(v[t]);
+      if (R == 5) dft5<DIR>(v[t]);
+      if (R == 8) dft8<DIR>(v[t]);
+      if (R == 9) dft9<DIR>(v[t]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int u = threadIdx.x + t * NT;
+    if (TASKS % NT == 0 || u < TASKS) {
+      const int l = u % NL, j = u / NL, k = j % NS;
+      const int base = (j / NS) * NS * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) put(base + r * NS, l, v[t][r], ax[t][r]);
+    }
+  }
+}
+
+// all passes of NL lines of length N held in LDS (element k of line l is
+// *at(k, l)); the last pass leaves through put with aux
+template <int N, int DIR, int NL, int NT, int P, int NS, class AT, class AUX, class PUT>
+__device__ __forceinline__ void lines_inplace(AT at, AUX aux, PUT put, const cplx* tw) {
+  constexpr Fac F = factor(N);
+  constexpr int R = F.r[P];
+  auto get = [=](int k, int l) { return *at(k, l); };
+  if constexpr (P == F.n - 1) {
+    pass_inplace<R, DIR, N, NS, NL, NT>(get, aux, put, tw);
+  } else {
+    pass_inplace<R, DIR, N, NS, NL, NT>(
+        get, [](int, int) { return 0; }, [=](int k, int l, cplx v, int) { *at(k, l) = v; }, tw);
+    __syncthreads();
+    lines_inplace<N, DIR, NL, NT, P + 1, NS * R>(at, aux, put, tw);
+  }
+}
+
+struct WPlaneArgs {
+  long nr, batch;
+  const real* f;         // [nr] factor of the transform (NULL: zero)
+  real s;                // and its scale
+  const double* X;       // rows of sphere coefficients to add, two per grid (or NULL)
+  const float* Xf;       // the same in FP32 (at most one of the two is set)
+  long nrow;             // rows held: the second row of the last grid may be absent
+  int npw, group;
+  const int *plane_sp, *plane_off, *ent_pos, *ent_code;
+  double s0, s1;         // 1/sqrt(Omega), 1/sqrt(2 Omega)
+};
+
+template <int N2, int N3>
+__global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N1, WPlaneArgs wa,
+                                                              const cplx* __restrict__ tw2,
+                                                              const cplx* __restrict__ tw3) {
+  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = wp_nt<N2, N3>();
+  static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
+  extern __shared__ cplx lds[];
+  cplx* P = lds;
+  long g;
+  int i1;
+  xcd_item(blockIdx.x, N1, wa.group != 0, g, i1);
+  if (g >= wa.batch) return;
+  cplx* gp = data + g * wa.nr + (long)i1 * NP2;
+  auto row = [=](int k, int l) { return P + l * RS + k; };  // element k of row l
+  auto col = [=](int k, int l) { return P + k * RS + l; };  // element k of column l
+  auto none = [](int, int) { return 0; };
+  if (wa.f) {
+#pragma unroll 4
+    for (int e = threadIdx.x; e < NP2; e += NT) P[e / N3 * RS + e % N3] = gp[e];
+    __syncthreads();
+    lines_inplace<N3, -1, N2, NT, 0, 1>(
+        row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+    __syncthreads();
+    const real* f = wa.f + (long)i1 * NP2;
+    const real s = wa.s;
+    lines_inplace<N2, -1, N3, NT, 0, 1>(
+        col, [=](int k, int l) { return f[k * N3 + l]; },
+        [=](int k, int l, cplx v, real m) {
+          m *= s;
+          v.x *= m;
+          v.y *= m;
+          *col(k, l) = v;
+        },
+        tw2);
+  } else {
+    for (int e = threadIdx.x; e < N2 * RS; e += NT) P[e] = mk(0.0, 0.0);
+  }
+  __syncthreads();
+  const int sp = wa.X || wa.Xf ? wa.plane_sp[i1] : -1;
+  if (sp >= 0) {
+    const long r1 = 2 * g * wa.npw;
+    const bool two = 2 * g + 1 < wa.nrow;
+    auto x = [&](long i) { return wa.X ? wa.X[i] : (double)wa.Xf[i]; };
+    for (int e = wa.plane_off[sp] + threadIdx.x; e < wa.plane_off[sp + 1]; e += NT) {
+      const int code = wa.ent_code[e], pos = wa.ent_pos[e];
+      double hx, hy;
+      if (code == 0) {
+        hx = x(r1) * wa.s0;
+        hy = two ? x(r1 + wa.npw) * wa.s0 : 0.0;
+      } else {
+        const long c = r1 + 2 * abs(code) - 1;
+        const double c1 = x(c), q1 = x(c + 1);
+        const double c2 = two ? x(c + wa.npw) : 0.0, q2 = two ? x(c + wa.npw + 1) : 0.0;
+        hx = (code > 0 ? c1 + q2 : c1 - q2) * wa.s1;
+        hy = (code > 0 ? c2 - q1 : q1 + c2) * wa.s1;
+      }
+      cplx* q = P + pos / N3 * RS + pos % N3;
+      *q = mk(q->x + hx, q->y + hy);
+    }
+    __syncthreads();
+  }
+  lines_inplace<N3, 1, N2, NT, 0, 1>(
+      row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+  __syncthreads();
+  lines_inplace<N2, 1, N3, NT, 0, 1>(
+      col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
 }
 
 template <int N>
@@ -995,7 +1177,7 @@ AxisArgs axis_args(const FftAxis& a) {
 #define BSEX_AXIS_SIZES(X) \
   X(8) X(12) X(16) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(60) X(64) X(72) X(80) X(96) X(120) X(128)
 #define BSEX_PLANE_SIZES(X) \
-  X(12, 12) X(16, 16) X(24, 24) X(32, 32) X(40, 40) X(48, 48) X(64, 64) X(72, 72) X(48, 120) X(120, 120)
+  X(12, 12) X(16, 16) X(24, 24) X(32, 32) X(40, 40) X(48, 48) X(64, 64) X(72, 72) X(48, 120)
 
 bool axis_ct_supported(int n) {
 #define C(N) \
@@ -1175,10 +1357,12 @@ int set_ct_lds_limits(int n2, int n3, int n1) {
     const void* fns[] = {(const void*)k_fft_plane_ct<A, B, -1, 0, 0>,                            \
                          (const void*)k_fft_plane_ct<A, B, 1, 0, 0>,                             \
                          (const void*)k_fft_plane_ct<A, B, 1, 1, 0>,                             \
-                         (const void*)k_fft_plane_ct<A, B, -1, 0, 1>,                            \
-                         (const void*)k_fft_plane_ct<A, B, -1, 0, 2>};                           \
+                         (const void*)k_fft_plane_ct<A, B, -1, 0, 1>};                           \
     for (const void* f : fns)                                                                    \
       BSE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, need));         \
+    BSE_HIP(hipFuncSetAttribute((const void*)k_w_plane<A, B>,                                    \
+                                hipFuncAttributeMaxDynamicSharedMemorySize,                      \
+                                (int)wp_lds<A, B>()));                                           \
   }
   BSEX_PLANE_SIZES(C)
 #undef C
@@ -1377,10 +1561,17 @@ static int launch_plane(const FftPlan& p, cplx* data, long batch, PlaneArgs pa, 
   const long groups = batch * pa.nplanes;
   if (groups <= 0) return BSE_OK;
   if (groups > 0x7fffffffL) return fail(BSE_EINVAL, "FFT batch too large");
-  if (p.ct_plane[BSEX_FFT_PREC])
-    launch_plane_ct<DIR, IN, OUT>(p.N[1], p.N[2], dim3((unsigned)groups), plane_ct_lds(p.N[1], p.N[2]),
-                                  st, data, pa, axis_args(p.ax[1]), axis_args(p.ax[2]));
-  else
+  // (OUT == 2 serves the planes without compile-time kernels: the others' W
+  // solves go through k_w_plane)
+  bool done = false;
+  if constexpr (OUT != 2) {
+    done = p.ct_plane[BSEX_FFT_PREC];
+    if (done)
+      launch_plane_ct<DIR, IN, OUT>(p.N[1], p.N[2], dim3((unsigned)groups),
+                                    plane_ct_lds(p.N[1], p.N[2]), st, data, pa,
+                                    axis_args(p.ax[1]), axis_args(p.ax[2]));
+  }
+  if (!done)
     hipLaunchKernelGGL((k_fft_plane<DIR, IN, OUT>), dim3((unsigned)groups), dim3(kPlaneThreads),
                        shm, st, data, pa, axis_args(p.ax[1]), axis_args(p.ax[2]));
   BSE_HIP(hipGetLastError());
@@ -1503,6 +1694,18 @@ static int axis_pairs(const FftPlan& p, const cplx* orb, int nv, const int2* IJ,
   return BSE_OK;
 }
 
+int pairs_axis(const FftPlan& p, const cplx* orb, int nv, const int2* IJ, long nblk, cplx* data,
+               hipStream_t st) {
+  if (nblk <= 0) return BSE_OK;
+  return axis_pairs(p, orb, nv, IJ, nullptr, 0, nblk * 32, data, st);
+}
+
+int times_axis(const FftPlan& p, const cplx* M, long nm, const cplx* x2, int xc, cplx* data,
+               hipStream_t st) {
+  if (nm <= 0) return BSE_OK;
+  return axis_pairs(p, M, 0, nullptr, x2, xc, nm, data, st);
+}
+
 int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const cplx* orb, int nv,
                     const int2* IJ, long nblk, cplx* data, const real* f, real s, cplx* compact,
                     hipStream_t st) {
@@ -1519,14 +1722,77 @@ int fft3d_fwd_times(const FftPlan& p, const SpherePlan& sp, const cplx* M, long 
   return plane_fwd_w(p, sp, data, nm, f, s, compact, st);
 }
 
+bool w_planes_supported(const FftPlan& p) { return p.ct_plane[BSEX_FFT_PREC]; }
+
+int fft3d_axis(const FftPlan& p, cplx* data, long batch, int dir, hipStream_t st) {
+  if (batch <= 0) return BSE_OK;
+  return x_pass(p, data, batch, dir, p.N[0], p.N[0], st);
+}
+
+int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, cplx* data, long batch, const real* f,
+                   real s, const double* X, const float* Xf, long nrow, double omega,
+                   hipStream_t st) {
+  if (batch <= 0) return BSE_OK;
+  if (!w_planes_supported(p)) return fail(BSE_EINVAL, "W planes: no kernel for this plane");
+  WPlaneArgs wa{};
+  wa.nr = p.nr;
+  wa.batch = batch;
+  wa.f = f;
+  wa.s = s;
+  wa.X = X;
+  wa.Xf = Xf;
+  wa.nrow = nrow;
+  wa.npw = sp.nent;
+  wa.group = xcd_group_on() ? 1 : 0;
+  wa.plane_sp = sp.plane_sp;
+  wa.plane_off = sp.plane_off;
+  wa.ent_pos = sp.ent_pos;
+  wa.ent_code = sp.ent_code;
+  wa.s0 = 1.0 / std::sqrt(omega);
+  wa.s1 = 1.0 / std::sqrt(2.0 * omega);
+  const long groups = (wa.group ? round8(batch) : batch) * p.N[0];
+  if (groups > 0x7fffffffL) return fail(BSE_EINVAL, "FFT batch too large");
+#define C(A, B)                                                                                  \
+  if (p.N[1] == A && p.N[2] == B) {                                                              \
+    hipLaunchKernelGGL((k_w_plane<A, B>), dim3((unsigned)groups), dim3(wp_nt<A, B>()),           \
+                       (wp_lds<A, B>()), st, data, p.N[0], wa, BSEX_FFT_TW(p.ax[1]),             \
+                       BSEX_FFT_TW(p.ax[2]));                                                    \
+    BSE_HIP(hipGetLastError());                                                                  \
+    return BSE_OK;                                                                               \
+  }
+  BSEX_PLANE_SIZES(C)
+#undef C
+  return fail(BSE_EINVAL, "W planes: no kernel for this plane");
+}
+
+// the sphere entries of the forward plane transforms of grids that have had
+// their axis-1 pass (the grids are left as they are)
+static int compact_planes(const FftPlan& p, const SpherePlan& sp, cplx* grid, long batch,
+                          cplx* compact, hipStream_t st) {
+  if (batch <= 0) return BSE_OK;
+  PlaneArgs pa{};
+  pa.nplanes = sp.nplanes;
+  pa.plane_i1 = sp.plane_i1;
+  pa.plane_off = sp.plane_off;
+  pa.ent_pos = sp.ent_pos;
+  pa.ent_code = sp.ent_code;
+  pa.nent = sp.nent;
+  pa.compact = compact;
+  if (launch_sphere(p, sp, false, grid, batch, pa, st)) {
+    BSE_HIP(hipGetLastError());
+    return BSE_OK;
+  }
+  return launch_plane<-1, 0, 1>(p, grid, batch, pa, st);
+}
+
 // fft3d(dir = +1) of the pair grids of nblk blocks, stored into the tau
 // layout by its last pass
 int fft3d_inv_store(const FftPlan& p, cplx* data, const int2* IJ, long nblk, const TauOut& o,
-                    hipStream_t st) {
+                    bool planes_done, hipStream_t st) {
   if (nblk <= 0) return BSE_OK;
   PlaneArgs pa{};
   pa.nplanes = p.N[0];
-  BSE_TRY((launch_plane<1, 0, 0>(p, data, nblk * 32, pa, st)));
+  if (!planes_done) BSE_TRY((launch_plane<1, 0, 0>(p, data, nblk * 32, pa, st)));
   const AxisArgs ax = axis_args(p.ax[0]);
   const int np2 = p.N[1] * p.N[2], n1 = p.N[0];
   int rc = BSE_OK;
@@ -1565,22 +1831,15 @@ int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const d
   return x_pass(p, grid, batch, +1, sp.nmax1, p.N[0], st);
 }
 
+int planes_to_compact(const FftPlan& p, const SpherePlan& sp, cplx* grid, long batch,
+                      cplx* compact, hipStream_t st) {
+  return compact_planes(p, sp, grid, batch, compact, st);
+}
+
 int grid_to_compact(const FftPlan& p, const SpherePlan& sp, cplx* grid, long batch,
                     cplx* compact, hipStream_t st) {
   if (batch <= 0) return BSE_OK;
   BSE_TRY(x_pass(p, grid, batch, -1, p.N[0], sp.nmax1, st));
-  PlaneArgs pa{};
-  pa.nplanes = sp.nplanes;
-  pa.plane_i1 = sp.plane_i1;
-  pa.plane_off = sp.plane_off;
-  pa.ent_pos = sp.ent_pos;
-  pa.ent_code = sp.ent_code;
-  pa.nent = sp.nent;
-  pa.compact = compact;
-  if (launch_sphere(p, sp, false, grid, batch, pa, st)) {
-    BSE_HIP(hipGetLastError());
-    return BSE_OK;
-  }
-  return launch_plane<-1, 0, 1>(p, grid, batch, pa, st);
+  return compact_planes(p, sp, grid, batch, compact, st);
 }
 

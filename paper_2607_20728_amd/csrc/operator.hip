@@ -324,6 +324,35 @@ static bool w_pairs_on(const bse_ctx* c, bool f32) {
   return on && w_fused_on() && fwd_pairs_supported(c->fft, f32);
 }
 
+// ... and with the whole plane part in one kernel where the plane has one
+static bool w_planes_on(const bse_ctx* c, bool f32) {
+  return w_fused_on() && w_planes_supported(c->fft, f32);
+}
+
+// v_c * g on ng complex grids (scale: 1/N_r times a factor)
+int poisson(bse_ctx* c, double2* g, long ng, double scale) {
+  if (w_planes_on(c, false)) {
+    BSE_TRY(fft3d_axis(c->fft, g, ng, -1, c->st));
+    BSE_TRY(fft3d_w_planes(c->fft, c->sp, g, ng, c->vc, scale, nullptr, nullptr, 0,
+                           c->basis.omega, c->st));
+    return fft3d_axis(c->fft, g, ng, +1, c->st);
+  }
+  BSE_TRY(fft3d(c->fft, g, ng, -1, c->st));
+  BSE_TRY(mul_real_field(g, ng, c->basis.nr, c->vc, scale, c->st));
+  return fft3d(c->fft, g, ng, +1, c->st);
+}
+static int poisson(bse_ctx* c, float2* g, long ng, float scale) {
+  if (w_planes_on(c, true)) {
+    BSE_TRY(fft3d_axis(c->fft, g, ng, -1, c->st));
+    BSE_TRY(fft3d_w_planes(c->fft, c->sp, g, ng, c->vc_f, scale, nullptr, nullptr, 0,
+                           c->basis.omega, c->st));
+    return fft3d_axis(c->fft, g, ng, +1, c->st);
+  }
+  BSE_TRY(fft3d(c->fft, g, ng, -1, c->st));
+  BSE_TRY(mul_real_field(g, ng, c->basis.nr, c->vc_f, scale, c->st));
+  return fft3d(c->fft, g, ng, +1, c->st);
+}
+
 int tau_build_range(bse_ctx* c, const double2* orbr, long gb0, long nblk, double* dst,
                     long dst_nblk, long dst_blk0, int mask, float* dstf) {
   if (nblk <= 0) return BSE_OK;
@@ -333,10 +362,19 @@ int tau_build_range(bse_ctx* c, const double2* orbr, long gb0, long nblk, double
   SphereMap m64 = c->map;
   const bool pdep = (mask & BSE_K_1D_PDEP) && c->npdep > 0;
   const bool bare = (mask & BSE_K_1D_BARE) != 0;
-  const bool fused = w_fused_on();
+  const bool planes = w_planes_on(c, false);
+  const bool fused = planes || w_fused_on();
   // the grids leave the forward transform times v_c / N_r, their sphere
   // entries in tile_cmp
-  if (w_pairs_on(c, false)) {
+  if (planes) {
+    if (w_pairs_on(c, false)) {
+      BSE_TRY(pairs_axis(c->fft, orbr, c->nv, c->blkIJ + gb0, nblk, c->tile_grids, c->st));
+    } else {
+      BSE_TRY(pair_density(orbr, c->nv, c->blkIJ + gb0, nblk, nr, c->tile_grids, c->st));
+      BSE_TRY(fft3d_axis(c->fft, c->tile_grids, ng, -1, c->st));
+    }
+    if (pdep) BSE_TRY(planes_to_compact(c->fft, c->sp, c->tile_grids, ng, c->tile_cmp, c->st));
+  } else if (w_pairs_on(c, false)) {
     BSE_TRY(fft3d_fwd_pairs(c->fft, c->sp, orbr, c->nv, c->blkIJ + gb0, nblk, c->tile_grids,
                             bare ? c->vc : nullptr, 1.0 / (double)nr,
                             pdep ? c->tile_cmp : nullptr, c->st));
@@ -362,7 +400,12 @@ int tau_build_range(bse_ctx* c, const double2* orbr, long gb0, long nblk, double
     BSE_TRY(mul_real_field(c->tile_grids, ng, nr, c->vc, 1.0 / (double)nr, c->st));
   else if (!fused)  // a fill kernel, not a memset: this may run inside a captured graph
     BSE_TRY(zero_fill(reinterpret_cast<double*>(c->tile_grids), 2 * ng * nr, c->st));
-  if (pdep) BSE_TRY(scatter_sets(m64, c->tile_F, 64, (int)nblk, c->tile_grids, 1, c->st));
+  if (planes)
+    BSE_TRY(fft3d_w_planes(c->fft, c->sp, c->tile_grids, ng, bare ? c->vc : nullptr,
+                           1.0 / (double)nr, pdep ? c->tile_F : nullptr, nullptr, ne,
+                           c->basis.omega, c->st));
+  else if (pdep)
+    BSE_TRY(scatter_sets(m64, c->tile_F, 64, (int)nblk, c->tile_grids, 1, c->st));
   if (fwd_pairs_supported(c->fft, false)) {
     TauOut o;
     if (dst) {
@@ -377,9 +420,10 @@ int tau_build_range(bse_ctx* c, const double2* orbr, long gb0, long nblk, double
       o.blk32 = gb0;
       o.sh32 = __builtin_ctz(c->Rf);
     }
-    return fft3d_inv_store(c->fft, c->tile_grids, c->blkIJ + gb0, nblk, o, c->st);
+    return fft3d_inv_store(c->fft, c->tile_grids, c->blkIJ + gb0, nblk, o, planes, c->st);
   }
-  BSE_TRY(fft3d(c->fft, c->tile_grids, ng, +1, c->st));
+  BSE_TRY(planes ? fft3d_axis(c->fft, c->tile_grids, ng, +1, c->st)
+                 : fft3d(c->fft, c->tile_grids, ng, +1, c->st));
   if (dstf)
     BSE_TRY(tau_store(c->tile_grids, c->blkIJ + gb0, nblk, nr, c->Rf, dstf, c->nblk, gb0, c->st));
   if (dst)
@@ -402,9 +446,18 @@ int tau_build_range_f(bse_ctx* c, const float2* orbr, long gb0, long nblk, float
   SphereMap m64 = c->map;
   const bool pdep = (mask & BSE_K_1D_PDEP) && c->npdep > 0;
   const bool bare = (mask & BSE_K_1D_BARE) != 0;
-  const bool fused = w_fused_on();
+  const bool planes = w_planes_on(c, true);
+  const bool fused = planes || w_fused_on();
   float2* cmp = reinterpret_cast<float2*>(c->tile_cmp);
-  if (w_pairs_on(c, true)) {
+  if (planes) {
+    if (w_pairs_on(c, true)) {
+      BSE_TRY(pairs_axis(c->fft, orbr, c->nv, c->blkIJ + gb0, nblk, tg, c->st));
+    } else {
+      BSE_TRY(pair_density(orbr, c->nv, c->blkIJ + gb0, nblk, nr, tg, c->st));
+      BSE_TRY(fft3d_axis(c->fft, tg, ng, -1, c->st));
+    }
+    if (pdep) BSE_TRY(planes_to_compact(c->fft, c->sp, tg, ng, cmp, c->st));
+  } else if (w_pairs_on(c, true)) {
     BSE_TRY(fft3d_fwd_pairs(c->fft, c->sp, orbr, c->nv, c->blkIJ + gb0, nblk, tg,
                             bare ? c->vc_f : nullptr, 1.0f / (float)nr, pdep ? cmp : nullptr,
                             c->st));
@@ -442,7 +495,11 @@ int tau_build_range_f(bse_ctx* c, const float2* orbr, long gb0, long nblk, float
     BSE_TRY(mul_real_field(tg, ng, nr, c->vc_f, 1.0f / (float)nr, c->st));
   else if (!fused)  // one float2 per double
     BSE_TRY(zero_fill(reinterpret_cast<double*>(tg), ng * nr, c->st));
-  if (f32)
+  if (planes)
+    BSE_TRY(fft3d_w_planes(c->fft, c->sp, tg, ng, bare ? c->vc_f : nullptr, 1.0f / (float)nr,
+                           pdep && !f32 ? c->tile_F : nullptr, f32 ? tf : nullptr, ne,
+                           c->basis.omega, c->st));
+  else if (f32)
     BSE_TRY(scatter_sets(m64, tf, 64, (int)nblk, tg, 1, c->st));
   else if (pdep)
     BSE_TRY(scatter_sets(m64, c->tile_F, 64, (int)nblk, tg, 1, c->st));
@@ -452,9 +509,9 @@ int tau_build_range_f(bse_ctx* c, const float2* orbr, long gb0, long nblk, float
     o.nblk32 = dst_nblk;
     o.blk32 = dst_blk0;
     o.sh32 = __builtin_ctz(c->Rf);
-    return fft3d_inv_store(c->fft, tg, c->blkIJ + gb0, nblk, o, c->st);
+    return fft3d_inv_store(c->fft, tg, c->blkIJ + gb0, nblk, o, planes, c->st);
   }
-  BSE_TRY(fft3d(c->fft, tg, ng, +1, c->st));
+  BSE_TRY(planes ? fft3d_axis(c->fft, tg, ng, +1, c->st) : fft3d(c->fft, tg, ng, +1, c->st));
   return tau_store(tg, c->blkIJ + gb0, nblk, nr, c->Rf, dst, dst_nblk, dst_blk0, c->st);
 }
 
@@ -543,9 +600,7 @@ int exchange_like(bse_ctx* c, const double2* L, const double2* M, const double2*
   double2* P = c->xpair;
   for (int v = 0; v < nx; ++v) {
     BSE_TRY(pair_times(M, c->nv, x + (long)(v >> 1) * nr, v & 1, nr, P, c->st));
-    BSE_TRY(fft3d(c->fft, P, c->nvh, -1, c->st));
-    BSE_TRY(mul_real_field(P, c->nvh, nr, c->vc, 1.0 / (double)nr, c->st));
-    BSE_TRY(fft3d(c->fft, P, c->nvh, +1, c->st));
+    BSE_TRY(poisson(c, P, c->nvh, 1.0 / (double)nr));
     BSE_TRY(contract_pairs(L, P, c->nv, nr, out + (long)(v >> 1) * nr, v & 1, scale, c->st));
   }
   return BSE_OK;
@@ -593,10 +648,19 @@ static int w_exchange_like(bse_ctx* c, const double2* L, const double2* M, const
   }
   double2* P = c->xpair;
   SphereMap m = c->map;
-  const bool fused = w_fused_on(), pairs = w_pairs_on(c, false);
+  const bool planes = w_planes_on(c, false);
+  const bool fused = planes || w_fused_on(), pairs = w_pairs_on(c, false);
   for (int v = 0; v < nx; ++v) {
     const double2* xv = x + (long)(v >> 1) * nr;
-    if (pairs) {
+    if (planes) {
+      if (pairs) {
+        BSE_TRY(times_axis(c->fft, M, c->nvh, xv, v & 1, P, c->st));
+      } else {
+        BSE_TRY(pair_times(M, nv, xv, v & 1, nr, P, c->st));
+        BSE_TRY(fft3d_axis(c->fft, P, c->nvh, -1, c->st));
+      }
+      if (pdep) BSE_TRY(planes_to_compact(c->fft, c->sp, P, c->nvh, c->wx_cmp, c->st));
+    } else if (pairs) {
       BSE_TRY(fft3d_fwd_times(c->fft, c->sp, M, c->nvh, xv, v & 1, P, bare ? c->vc : nullptr,
                               1.0 / (double)nr, pdep ? c->wx_cmp : nullptr, c->st));
     } else {
@@ -619,8 +683,14 @@ static int w_exchange_like(bse_ctx* c, const double2* L, const double2* M, const
       BSE_TRY(mul_real_field(P, c->nvh, nr, c->vc, 1.0 / (double)nr, c->st));
     else if (!fused)
       BSE_TRY(zero_fill(reinterpret_cast<double*>(P), 2L * c->nvh * nr, c->st));
-    if (pdep) BSE_TRY(scatter_sets(m, c->wx_F, nv, 1, P, 1, c->st));
-    BSE_TRY(fft3d(c->fft, P, c->nvh, +1, c->st));
+    if (planes) {
+      BSE_TRY(fft3d_w_planes(c->fft, c->sp, P, c->nvh, bare ? c->vc : nullptr, 1.0 / (double)nr,
+                             pdep ? c->wx_F : nullptr, nullptr, nv, c->basis.omega, c->st));
+      BSE_TRY(fft3d_axis(c->fft, P, c->nvh, +1, c->st));
+    } else {
+      if (pdep) BSE_TRY(scatter_sets(m, c->wx_F, nv, 1, P, 1, c->st));
+      BSE_TRY(fft3d(c->fft, P, c->nvh, +1, c->st));
+    }
     BSE_TRY(contract_pairs(L, P, nv, nr, out + (long)(v >> 1) * nr, v & 1, scale, c->st));
   }
   return BSE_OK;
@@ -641,9 +711,7 @@ int apply_coupling(bse_ctx* c, int nb, const double* X, double* Y) {
     if (c->kmask & BSE_K_1E) {
       const long nbh = (k + 1) / 2;
       BSE_TRY(transition_density(c->phir, c->agrid, c->nv, k, nr, c->drho, c->st));
-      BSE_TRY(fft3d(c->fft, c->drho, nbh, -1, c->st));
-      BSE_TRY(mul_real_field(c->drho, nbh, nr, c->vc, 1.0 / (double)nr, c->st));
-      BSE_TRY(fft3d(c->fft, c->drho, nbh, +1, c->st));
+      BSE_TRY(poisson(c, c->drho, nbh, 1.0 / (double)nr));
       BSE_TRY(combine(c->agrid, c->phir, c->Vr, c->drho, nullptr, z, c->nv, k, nr, c->spin, 0,
                       c->st));
     } else {
@@ -675,9 +743,7 @@ int apply_chunk(bse_ctx* c, int nb, const double* X, double* Y) {
     PhaseScope ps(c, PH_K1E);
     const long nbh = (nb + 1) / 2;
     BSE_TRY(transition_density(c->phik, c->agrid, c->nv, nb, nr, c->drho, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho, nbh, -1, c->st));
-    BSE_TRY(mul_real_field(c->drho, nbh, nr, c->vc, 1.0 / (double)nr, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho, nbh, +1, c->st));
+    BSE_TRY(poisson(c, c->drho, nbh, 1.0 / (double)nr));
     vdrho = c->drho;
   }
   const int with_v = (c->kmask & BSE_K_D) ? 1 : 0;
@@ -735,9 +801,7 @@ int kernel_part(bse_ctx* c, const double2* agrid, double* Kt) {
   const double2* vdrho = nullptr;
   if (c->kmask & BSE_K_1E) {
     BSE_TRY(transition_density(c->phik, agrid, c->nv, 1, nr, c->drho, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho, 1, -1, c->st));
-    BSE_TRY(mul_real_field(c->drho, 1, nr, c->vc, 1.0 / (double)nr, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho, 1, +1, c->st));
+    BSE_TRY(poisson(c, c->drho, 1, 1.0 / (double)nr));
     vdrho = c->drho;
   }
   const double2* yk = nullptr;
@@ -851,9 +915,7 @@ int apply_chunk_mixed(bse_ctx* c, int nb, const double* X, double* Y) {
     PhaseScope ps(c, PH_K1E);
     const long nbh = (nb + 1) / 2;
     BSE_TRY(transition_density(c->phik_f, c->agrid_f, c->nv, nb, nr, c->drho_f, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho_f, nbh, -1, c->st));
-    BSE_TRY(mul_real_field(c->drho_f, nbh, nr, c->vc_f, 1.0f / (float)nr, c->st));
-    BSE_TRY(fft3d(c->fft, c->drho_f, nbh, +1, c->st));
+    BSE_TRY(poisson(c, c->drho_f, nbh, 1.0f / (float)nr));
     vdrho = c->drho_f;
   }
   const int with_v = (c->kmask & BSE_K_D) ? 1 : 0;

@@ -823,9 +823,7 @@ static int ks_fields(bse_ctx* c, const double2* phir, double* vhxc) {
   double2* rho = reinterpret_cast<double2*>(rg.p);
   BSE_TRY(occupied_density(phir, c->nv, nr, rho, c->st));  // (sum phi^2, 0)
   BSE_TRY(xc_fields(rho, nr, 2.0, c->rho_floor, vx.p, c->fxc, c->rho_ks, c->st));
-  BSE_TRY(fft3d(c->fft, rho, 1, -1, c->st));
-  BSE_TRY(mul_real_field(rho, 1, nr, c->vc, 2.0 / (double)nr, c->st));
-  BSE_TRY(fft3d(c->fft, rho, 1, +1, c->st));
+  BSE_TRY(poisson(c, rho, 1, 2.0 / (double)nr));
   BSE_TRY(real_part(rho, nr, vhxc, c->st));
   return axpby(1.0, vx.p, 1.0, vhxc, nr, c->st);
 }
@@ -942,9 +940,7 @@ int ks_ground_state(bse_ctx* c, int n_want) {
 static int ks_hxc_apply(bse_ctx* c, double2* w, double2* t) {
   const long nr = c->basis.nr;
   BSE_HIP(hipMemcpyAsync(t, w, sizeof(double2) * nr, hipMemcpyDeviceToDevice, c->st));
-  BSE_TRY(fft3d(c->fft, w, 1, -1, c->st));
-  BSE_TRY(mul_real_field(w, 1, nr, c->vc, 1.0 / (double)nr, c->st));
-  BSE_TRY(fft3d(c->fft, w, 1, +1, c->st));
+  BSE_TRY(poisson(c, w, 1, 1.0 / (double)nr));
   return hxc_field(w, t, c->fxc, 1, nr, 1.0, c->st);
 }
 
