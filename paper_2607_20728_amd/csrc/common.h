@@ -218,17 +218,23 @@ int dgemm_from(int ta, int tb, long M, long N, long K, double alpha, const doubl
                const double* B, long ldb, double beta, const double* Cin, double* C, long ldc,
                hipStream_t st);
 // dgemm with K split across workgroups when the output tiles are too few to
-// fill the device (partials in `work`, summed in a fixed order)
+// fill the device (partials in `work`, summed in a fixed order).
+// fill (here and in dgemm_tall, row_dots): split further while the launch
+// leaves the device idle.  false keeps every chunk at 1024 or more, and with
+// it the last bits of the sums.  The ground state and the eigensolvers'
+// starting blocks take that: they diagonalise Gram matrices that are the
+// identity up to rounding, so the signs (and, among degenerate states, the
+// choice) of the vectors they return hang on those bits.
 int dgemm_ws(int ta, int tb, long M, long N, long K, double alpha, const double* A, long lda,
              const double* B, long ldb, double beta, double* C, long ldc, double* work,
-             long work_len, hipStream_t st);
-long dgemm_work(long M, long N, long K);
+             long work_len, hipStream_t st, bool fill = true);
+long dgemm_work(long M, long N, long K, bool fill = true);
 // C[M][N] = alpha A[M][K] B[N][K]^T + beta C for small M, N and long K
 // (split over K with a fixed-order reduction; work buffer owned by the caller).
 int dgemm_tall(long M, long N, long K, double alpha, const double* A, long lda,
                const double* B, long ldb, double beta, double* C, long ldc,
-               double* work, long work_len, hipStream_t st);
-long dgemm_tall_work(long M, long N, long K);
+               double* work, long work_len, hipStream_t st, bool fill = true);
+long dgemm_tall_work(long M, long N, long K, bool fill = true);
 
 // ---- host dense linear algebra ------------------------------------------------------
 // Symmetric eigen-decomposition: A[n][n] row-major (overwritten by eigenvectors,

@@ -170,9 +170,10 @@ struct PhaseScope {
 int prof_collect(bse_ctx* c);
 
 // operator pieces (device, stream ordered)
-int proj_c(bse_ctx* c, const double* X, double* Y, int nset);
+int proj_c(bse_ctx* c, const double* X, double* Y, int nset, bool fill = true);
+int ensure_gw(bse_ctx* c, long need);
 int gemm(bse_ctx* c, int ta, int tb, long M, long N, long K, double alpha, const double* A,
-         long lda, const double* B, long ldb, double beta, double* C, long ldc);
+         long lda, const double* B, long ldb, double beta, double* C, long ldc, bool fill = true);
 int apply_chunk(bse_ctx* c, int nb, const double* X, double* Y);
 int apply_H(bse_ctx* c, int nvs, int nset, const double* X, double* Y, double2* grids,
             double shift, const double* eps, int project);
@@ -217,7 +218,8 @@ int ks_potential_from_orbitals(bse_ctx* c);
 // out_v += scale sum_w L_w (v_c * (M_w x_v)), v < nx (packed grids)
 int exchange_like(bse_ctx* c, const double2* L, const double2* M, const double2* x, int nx,
                   double2* out, double scale);
-int gram_tall(bse_ctx* c, const double* A, long m, const double* B, long n, long len, double* C);
+int gram_tall(bse_ctx* c, const double* A, long m, const double* B, long n, long len, double* C,
+              bool fill = true);
 // device address of the allocation-free scratch on `dev` (called once per
 // context initialisation, with that device current)
 int noalloc_setup(int dev);

@@ -30,6 +30,13 @@ constexpr int BN = 64, BK = 16;
 // rows of the workgroup tile for an M-row output
 inline int bm_for(long M) { return M <= 16 ? 16 : 64; }
 
+// A launch of few workgroups waits for its loads: each K step ends at a
+// barrier behind the next step's tiles.  Such launches take K steps of 64
+// (and 32 x 32 tiles instead of 64 x 64, four times as many workgroups), so
+// there are a quarter of the waits.  Every output element still sums its K
+// in the same order, so results do not change.
+constexpr int BKF = 64, BMF = 32;
+
 template <typename T>
 struct MfmaOf;
 template <>
@@ -51,14 +58,15 @@ struct MfmaOf<float> {
 };
 
 // one workgroup tile of C = alpha op(A) op(B) + beta C (in T, accumulated in T)
-template <typename T, int TA, int TB, int BM>
+template <typename T, int TA, int TB, int BM, int BN, int BK>
 __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
                                           const T* __restrict__ A, long lda,
                                           const T* __restrict__ B, long ldb, T beta,
                                           const T* Cin, T* __restrict__ C, long ldc,
-                                          long k_chunk, long c_split_stride) {
+                                          long k_chunk, long c_split_stride, int ntn,
+                                          int by_row) {
   typedef MfmaOf<T> MF;
-  constexpr int WGM = BM == 64 ? 2 : 1;  // waves along M
+  constexpr int WGM = BM >= 32 ? 2 : 1;  // waves along M
   constexpr int WGN = 4 / WGM;           // waves along N
   constexpr int TM = BM / (16 * WGM);    // MFMA tiles per wave along M
   constexpr int TN = BN / (16 * WGN);    // and along N
@@ -68,8 +76,17 @@ __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  const long m0 = (long)blockIdx.y * BM;
-  const long n0 = (long)blockIdx.x * BN;
+  long mt;
+  int nt;
+  if (by_row) {  // a row of tiles on one XCD, which reads its A rows once
+    xcd_item(blockIdx.x, ntn, true, mt, nt);
+    if (mt * BM >= M) return;
+  } else {  // tile columns spread over the XCDs, each reading its B columns
+    mt = blockIdx.x / ntn;
+    nt = (int)(blockIdx.x % ntn);
+  }
+  const long m0 = mt * BM;
+  const long n0 = (long)nt * BN;
   const long kb = (long)blockIdx.z * k_chunk;
   const long ke = min(K, kb + k_chunk);
   typename MF::acc_t acc[TM][TN];
@@ -165,89 +182,152 @@ __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
       }
 }
 
-template <int TA, int TB, int BM>
+template <int TA, int TB, int BM, int BN, int BK>
 __global__ __launch_bounds__(256) void k_dgemm(long M, long N, long K, double alpha,
                                                const double* __restrict__ A, long lda,
                                                const double* __restrict__ B, long ldb,
                                                double beta, const double* Cin,
                                                double* __restrict__ C, long ldc, long k_chunk,
-                                               long c_split_stride) {
-  gemm_tile<double, TA, TB, BM>(M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, k_chunk,
-                                c_split_stride);
+                                               long c_split_stride, int ntn, int by_row) {
+  gemm_tile<double, TA, TB, BM, BN, BK>(M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, k_chunk,
+                                        c_split_stride, ntn, by_row);
 }
 
-template <int TA, int TB, int BM>
+template <int TA, int TB, int BM, int BN, int BK>
 __global__ __launch_bounds__(256) void k_sgemm(long M, long N, long K, float alpha,
                                                const float* __restrict__ A, long lda,
                                                const float* __restrict__ B, long ldb,
                                                float beta, const float* Cin,
                                                float* __restrict__ C, long ldc, long k_chunk,
-                                               long c_split_stride) {
-  gemm_tile<float, TA, TB, BM>(M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, k_chunk,
-                               c_split_stride);
+                                               long c_split_stride, int ntn, int by_row) {
+  gemm_tile<float, TA, TB, BM, BN, BK>(M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, k_chunk,
+                                       c_split_stride, ntn, by_row);
 }
 
-// C = alpha * sum_z P[z] + beta * C, fixed order over z
-__global__ void k_reduce_split(long M, long N, int nz, const double* __restrict__ P, long pstride,
-                               double alpha, double beta, double* __restrict__ C, long ldc) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+// C = alpha * sum_z P[z] + beta * C, z ascending.  ZL > 1: ZL threads load an
+// element's partials, ZL of them at a time each, into LDS, and one sums them
+// there (one thread that loaded and added 512 in turn took 10 us and more).
+template <int ZL>
+__global__ __launch_bounds__(256) void k_reduce_split(long M, long N, int nz,
+                                                      const double* __restrict__ P, long pstride,
+                                                      double alpha, double beta,
+                                                      double* __restrict__ C, long ldc) {
+  constexpr int NE = 256 / ZL;
+  const int el = threadIdx.x % NE, zl = threadIdx.x / NE;
+  const long e = (long)blockIdx.x * NE + el;
+  double s = 0.0;
+  if constexpr (ZL == 1) {
+    if (e < M * N) {
+#pragma unroll 8
+      for (int z = 0; z < nz; ++z) s += P[z * pstride + e];
+    }
+  } else {
+    __shared__ double red[ZL * ZL][NE];
+    for (int z0 = 0; z0 < nz; z0 += ZL * ZL) {
+      double v[ZL];
+#pragma unroll
+      for (int q = 0; q < ZL; ++q) {
+        const int z = z0 + q * ZL + zl;
+        v[q] = z < nz && e < M * N ? P[z * pstride + e] : 0.0;
+      }
+      if (z0 > 0) __syncthreads();
+#pragma unroll
+      for (int q = 0; q < ZL; ++q) red[q * ZL + zl][el] = v[q];
+      __syncthreads();
+      const int n = min(ZL * ZL, nz - z0);
+      if (zl == 0) {
+#pragma unroll 8
+        for (int z = 0; z < n; ++z) s += red[z][el];
+      }
+    }
+    if (zl > 0) return;
+  }
   if (e >= M * N) return;
   const long m = e / N, n = e % N;
-  double s = 0.0;
-  for (int z = 0; z < nz; ++z) s += P[z * pstride + m * N + n];
   double v = alpha * s;
   if (beta != 0.0) v += beta * C[m * ldc + n];
   C[m * ldc + n] = v;
+}
+
+void reduce_split(long M, long N, int nz, const double* P, double alpha, double beta, double* C,
+                  long ldc, hipStream_t st) {
+  const long tot = M * N;
+  if (nz > 16)
+    hipLaunchKernelGGL(k_reduce_split<16>, dim3((unsigned)((tot + 15) / 16)), dim3(256), 0, st, M,
+                       N, nz, P, tot, alpha, beta, C, ldc);
+  else
+    hipLaunchKernelGGL(k_reduce_split<1>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, M,
+                       N, nz, P, tot, alpha, beta, C, ldc);
 }
 
 }  // namespace
 
 namespace {
 
-void launch(int ta, int tb, int bm, dim3 grid, hipStream_t st, long M, long N, long K,
-            double alpha, const double* A, long lda, const double* B, long ldb, double beta,
-            const double* Cin, double* C, long ldc, long kc, long cstride) {
-#define L3(TA_, TB_, BM_)                                                                      \
-  hipLaunchKernelGGL((k_dgemm<TA_, TB_, BM_>), grid, dim3(256), 0, st, M, N, K, alpha, A, lda, \
-                     B, ldb, beta, Cin, C, ldc, kc, cstride)
-#define L2(TA_, TB_)    \
-  if (bm == 16)         \
-    L3(TA_, TB_, 16);   \
-  else                  \
-    L3(TA_, TB_, 64)
-  if (!ta && !tb)
-    L2(0, 0);
-  else if (!ta && tb)
-    L2(0, 1);
-  else if (ta && !tb)
-    L2(1, 0);
-  else
-    L2(1, 1);
-#undef L2
-#undef L3
+// the tiles of a launch with s K splits: 64 x 64 (16 x 64 up to 16 rows) in K
+// steps of 16, or the latency forms when that gives fewer than `few` workgroups
+struct Tiling {
+  int bm, bn, bk;
+  long mt, nt;
+};
+Tiling tiling(long M, long N, long K, long s, long few) {
+  Tiling t{M <= 16 ? 16 : 64, BN, BK, 0, 0};
+  t.mt = (M + t.bm - 1) / t.bm;
+  t.nt = (N + t.bn - 1) / t.bn;
+  if (t.mt * t.nt * s < few && K >= 2 * BKF) {
+    t.bk = BKF;
+    if (t.bm == 64) t.bm = t.bn = BMF;
+    t.mt = (M + t.bm - 1) / t.bm;
+    t.nt = (N + t.bn - 1) / t.bn;
+  }
+  return t;
 }
 
-void launch_s(int ta, int tb, int bm, dim3 grid, hipStream_t st, long M, long N, long K,
-              float alpha, const float* A, long lda, const float* B, long ldb, float beta,
-              float* C, long ldc) {
-#define L3(TA_, TB_, BM_)                                                                      \
-  hipLaunchKernelGGL((k_sgemm<TA_, TB_, BM_>), grid, dim3(256), 0, st, M, N, K, alpha, A, lda, \
-                     B, ldb, beta, (const float*)nullptr, C, ldc, K > 0 ? K : 1, 0L)
-#define L2(TA_, TB_)    \
-  if (bm == 16)         \
-    L3(TA_, TB_, 16);   \
-  else                  \
-    L3(TA_, TB_, 64)
-  if (!ta && !tb)
-    L2(0, 0);
-  else if (!ta && tb)
-    L2(0, 1);
-  else if (ta && !tb)
-    L2(1, 0);
+template <typename T, int TA, int TB, int BM, int BN_, int BK_, typename... Args>
+void launch_tile(dim3 grid, hipStream_t st, Args... args) {
+  if constexpr (sizeof(T) == 8)
+    hipLaunchKernelGGL((k_dgemm<TA, TB, BM, BN_, BK_>), grid, dim3(256), 0, st, args...);
   else
-    L2(1, 1);
-#undef L2
-#undef L3
+    hipLaunchKernelGGL((k_sgemm<TA, TB, BM, BN_, BK_>), grid, dim3(256), 0, st, args...);
+}
+
+template <typename T, int TA, int TB, typename... Args>
+void launch_form(const Tiling& t, dim3 grid, hipStream_t st, Args... args) {
+  if (t.bm == 16)
+    t.bk == BKF ? launch_tile<T, TA, TB, 16, BN, BKF>(grid, st, args...)
+                : launch_tile<T, TA, TB, 16, BN, BK>(grid, st, args...);
+  else
+    t.bk == BKF ? launch_tile<T, TA, TB, BMF, BMF, BKF>(grid, st, args...)
+                : launch_tile<T, TA, TB, 64, BN, BK>(grid, st, args...);
+}
+
+// few: below this many workgroups the latency forms serve.  FP64 fills a
+// CU's matrix units from one workgroup, FP32 (half the time per instruction)
+// needs more in flight.
+template <typename T>
+int launch(int ta, int tb, long M, long N, long K, T alpha, const T* A, long lda, const T* B,
+           long ldb, T beta, const T* Cin, T* C, long ldc, long kc, long cstride, long s,
+           hipStream_t st) {
+  const Tiling t = tiling(M, N, K, s, sizeof(T) == 8 ? 256 : 512);
+  const int by_row = t.nt < t.mt && xcd_group_on() ? 1 : 0;
+  const long nwg = (by_row ? round8(t.mt) : t.mt) * t.nt;
+  if (nwg > 0x7fffffffL || s > 65535) return fail(BSE_EINVAL, "gemm: output too large for the grid");
+  const dim3 grid((unsigned)nwg, 1, (unsigned)s);
+  const int ntn = (int)t.nt;
+#define GO(TA_, TB_)                                                                             \
+  launch_form<T, TA_, TB_>(t, grid, st, M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, kc, \
+                           cstride, ntn, by_row)
+  if (!ta && !tb)
+    GO(0, 0);
+  else if (!ta && tb)
+    GO(0, 1);
+  else if (ta && !tb)
+    GO(1, 0);
+  else
+    GO(1, 1);
+#undef GO
+  BSE_HIP(hipGetLastError());
+  return BSE_OK;
 }
 
 long tiles_of(long M, long N) {
@@ -265,61 +345,59 @@ int dgemm(int ta, int tb, long M, long N, long K, double alpha, const double* A,
 int sgemm(int ta, int tb, long M, long N, long K, float alpha, const float* A, long lda,
           const float* B, long ldb, float beta, float* C, long ldc, hipStream_t st) {
   if (M <= 0 || N <= 0) return BSE_OK;
-  const int bm = bm_for(M);
-  const dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + bm - 1) / bm), 1);
-  if (grid.y > 65535) return fail(BSE_EINVAL, "sgemm: M too large for the grid");
   if (K <= 0) alpha = 0.0f;
-  launch_s(ta, tb, bm, grid, st, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  BSE_HIP(hipGetLastError());
-  return BSE_OK;
+  return launch<float>(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, nullptr, C, ldc,
+                       K > 0 ? K : 1, 0L, 1, st);
 }
 
 int dgemm_from(int ta, int tb, long M, long N, long K, double alpha, const double* A, long lda,
                const double* B, long ldb, double beta, const double* Cin, double* C, long ldc,
                hipStream_t st) {
   if (M <= 0 || N <= 0) return BSE_OK;
-  const int bm = bm_for(M);
-  const dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + bm - 1) / bm), 1);
-  if (grid.y > 65535) return fail(BSE_EINVAL, "dgemm: M too large for the grid");
-  const long kc = K > 0 ? K : 1;
   if (K <= 0) alpha = 0.0;
-  launch(ta, tb, bm, grid, st, M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, kc, 0L);
-  BSE_HIP(hipGetLastError());
-  return BSE_OK;
+  return launch<double>(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, Cin, C, ldc, K > 0 ? K : 1,
+                        0L, 1, st);
+}
+
+// K splits that raise `s` splits of `tiles` output tiles to about 1024
+// workgroups (4 per CU) with chunks of at least KMIN: the products of small
+// systems have few tiles and a short K, and run for as long as one
+// workgroup's walk over its chunk.
+// Chunks of at least 1024 only took 49 us for 16 x 80 x 1503, now 7; 61 us for
+// 48 x 160 x 3695, now 13; 78 us for 96 x 96 x 6979, now 20.
+constexpr long KMIN = 128;
+static long fill_splits(long tiles, long s, long K) {
+  if (tiles * s >= 1024) return s;
+  return std::max(s, std::min(1024 / tiles, K / KMIN));
 }
 
 // split-K factor for an op(A) op(B) product whose tile grid is small: aim at
 // ~4096 workgroups (16 per CU, so global-load latency is hidden by occupancy)
-// with K chunks of at least 1024
-static long k_splits(long M, long N, long K) {
+// with K chunks of at least 1024, at 1024 workgroups with shorter ones
+static long k_splits(long M, long N, long K, bool fill) {
   const long tiles = tiles_of(M, N);
-  if (tiles >= 2048 || K < 2048) return 1;
-  long s = std::min((K + 1023) / 1024, std::max(1L, 4096 / tiles));
-  return std::max(s, 1L);
+  if (tiles >= 2048) return 1;
+  const long s = K < 2048 ? 1 : std::min((K + 1023) / 1024, std::max(1L, 4096 / tiles));
+  return std::max(fill ? fill_splits(tiles, s, K) : s, 1L);
 }
 
-long dgemm_work(long M, long N, long K) {
-  const long s = k_splits(M, N, K);
+long dgemm_work(long M, long N, long K, bool fill) {
+  const long s = k_splits(M, N, K, fill);
   return s > 1 ? s * M * N : 0;
 }
 
 int dgemm_ws(int ta, int tb, long M, long N, long K, double alpha, const double* A, long lda,
              const double* B, long ldb, double beta, double* C, long ldc, double* work,
-             long work_len, hipStream_t st) {
-  long s = k_splits(M, N, K);
+             long work_len, hipStream_t st, bool fill) {
+  long s = k_splits(M, N, K, fill);
   if (s <= 1 || !work || s * M * N > work_len)
     return dgemm(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, st);
   long kc = (K + s - 1) / s;
   kc = ((kc + BK - 1) / BK) * BK;
   s = (K + kc - 1) / kc;
-  const int bm = bm_for(M);
-  const dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + bm - 1) / bm), (unsigned)s);
-  if (grid.y > 65535) return fail(BSE_EINVAL, "dgemm: M too large for the grid");
-  launch(ta, tb, bm, grid, st, M, N, K, 1.0, A, lda, B, ldb, 0.0, nullptr, work, N, kc, M * N);
-  BSE_HIP(hipGetLastError());
-  const long tot = M * N;
-  hipLaunchKernelGGL(k_reduce_split, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, M, N,
-                     (int)s, work, M * N, alpha, beta, C, ldc);
+  BSE_TRY(launch<double>(ta, tb, M, N, K, 1.0, A, lda, B, ldb, 0.0, nullptr, work, N, kc, M * N, s,
+                         st));
+  reduce_split(M, N, (int)s, work, alpha, beta, C, ldc, st);
   BSE_HIP(hipGetLastError());
   return BSE_OK;
 }
@@ -327,35 +405,33 @@ int dgemm_ws(int ta, int tb, long M, long N, long K, double alpha, const double*
 // K splits of a product with a long K: about TALL_TARGET workgroups in all,
 // K chunks of at least 1024
 constexpr long TALL_TARGET = 1024;
-static long tall_splits(long M, long N, long K) {
+static long tall_splits(long M, long N, long K, bool fill) {
   const long tiles = tiles_of(M, N);
   long s = TALL_TARGET / (tiles > 0 ? tiles : 1);
   const long maxs = (K + 1023) / 1024;
   if (s > maxs) s = maxs;
-  if (s < 1) s = 1;
-  return s;
+  if (fill) s = fill_splits(tiles > 0 ? tiles : 1, s, K);
+  return std::max(s, 1L);
 }
 
-long dgemm_tall_work(long M, long N, long K) { return tall_splits(M, N, K) * M * N; }
+long dgemm_tall_work(long M, long N, long K, bool fill) {
+  return tall_splits(M, N, K, fill) * M * N;
+}
 
 int dgemm_tall(long M, long N, long K, double alpha, const double* A, long lda, const double* B,
                long ldb, double beta, double* C, long ldc, double* work, long work_len,
-               hipStream_t st) {
+               hipStream_t st, bool fill) {
   if (M <= 0 || N <= 0) return BSE_OK;
-  long s = tall_splits(M, N, K);
+  long s = tall_splits(M, N, K, fill);
   if (s * M * N > work_len) return fail(BSE_EINVAL, "dgemm_tall: work buffer too small");
   long kc = (K + s - 1) / s;
   kc = ((kc + BK - 1) / BK) * BK;
   if (kc < BK) kc = BK;
   s = (K + kc - 1) / kc;
   if (s < 1) s = 1;
-  const int bm = bm_for(M);
-  const dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + bm - 1) / bm), (unsigned)s);
-  launch(0, 1, bm, grid, st, M, N, K, 1.0, A, lda, B, ldb, 0.0, nullptr, work, N, kc, M * N);
-  BSE_HIP(hipGetLastError());
-  const long tot = M * N;
-  hipLaunchKernelGGL(k_reduce_split, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, M, N,
-                     (int)s, work, M * N, alpha, beta, C, ldc);
+  BSE_TRY(launch<double>(0, 1, M, N, K, 1.0, A, lda, B, ldb, 0.0, nullptr, work, N, kc, M * N, s,
+                         st));
+  reduce_split(M, N, (int)s, work, alpha, beta, C, ldc, st);
   BSE_HIP(hipGetLastError());
   return BSE_OK;
 }

@@ -150,8 +150,8 @@ long force_reduce_work(int nsites, long nr);
 // out[i] = sum_j A[i*len + j] * B[i*len + j], i < rows (fixed-order split
 // reduction through `work`, which must hold row_dots_work(rows, len) doubles)
 int row_dots(const double* A, const double* B, long rows, long len, double* out, double* work,
-             long work_len, hipStream_t st);
-long row_dots_work(long rows, long len);
+             long work_len, hipStream_t st, bool fill = true);
+long row_dots_work(long rows, long len, bool fill = true);
 // Y[i][j] = a[i] * X[i][j] + b[i] * Y[i][j]  (a or b NULL means 1)
 int row_axpby(const double* a, const double* X, const double* b, double* Y, long rows, long len,
               hipStream_t st);

@@ -910,6 +910,7 @@ __global__ __launch_bounds__(256) void k_row_dots(const double* __restrict__ A,
   const double* a = A + row * len;
   const double* b = B + row * len;
   double s = 0.0;
+#pragma unroll 8
   for (long j = j0 + threadIdx.x; j < j1; j += 256) s += a[j] * b[j];
   red[threadIdx.x] = s;
   __syncthreads();
@@ -920,13 +921,18 @@ __global__ __launch_bounds__(256) void k_row_dots(const double* __restrict__ A,
   if (threadIdx.x == 0) part[row * nsplit + blockIdx.x] = red[0];
 }
 
-__global__ void k_row_dots_final(const double* __restrict__ part, long rows, int nsplit,
-                                 double* __restrict__ out) {
-  const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
+// one wave per row: 64 partials loaded at once, summed in order (one thread
+// that walked them took 20 us for 300)
+__global__ __launch_bounds__(64) void k_row_dots_final(const double* __restrict__ part, int nsplit,
+                                                       double* __restrict__ out) {
+  const long r = blockIdx.x;
   double s = 0.0;
-  for (int q = 0; q < nsplit; ++q) s += part[r * nsplit + q];
-  out[r] = s;
+  for (int q0 = 0; q0 < nsplit; q0 += 64) {
+    const int n = min(64, nsplit - q0);
+    const double v = (int)threadIdx.x < n ? part[r * nsplit + q0 + threadIdx.x] : 0.0;
+    for (int l = 0; l < n; ++l) s += __shfl(v, l);
+  }
+  if (threadIdx.x == 0) out[r] = s;
 }
 
 __global__ void k_zero(double* __restrict__ p, long n) {
@@ -1565,25 +1571,29 @@ int force_reduce(const double2* rhoG, const double* xyz, const double* depth, co
   return BSE_OK;
 }
 
-static int row_dots_split(long rows, long len) {
-  // ~64k elements per block, at most 512 blocks per row and 64k blocks in all
+static int row_dots_split(long rows, long len, bool fill) {
+  // ~64k elements per block, at most 512 blocks per row and 64k blocks in all;
+  // shorter chunks, of at least 1024, while there are fewer than 512 blocks
+  // (one block per row of 122,000 took 48 us, now 6)
   long ns = std::max(1L, std::min(512L, len / 65536));
+  if (fill && rows > 0 && rows * ns < 512) ns = std::max(ns, std::min(512 / rows, len / 1024));
   while (ns > 1 && rows * ns > 65536) ns /= 2;
-  return (int)ns;
+  return (int)std::max(ns, 1L);
 }
 
-long row_dots_work(long rows, long len) { return rows * row_dots_split(rows, len); }
+long row_dots_work(long rows, long len, bool fill) {
+  return rows * row_dots_split(rows, len, fill);
+}
 
 int row_dots(const double* A, const double* B, long rows, long len, double* out, double* work,
-             long work_len, hipStream_t st) {
+             long work_len, hipStream_t st, bool fill) {
   if (rows <= 0) return BSE_OK;
   if (rows > 65535) return fail(BSE_EINVAL, "row_dots: too many rows");
-  const int ns = row_dots_split(rows, len);
+  const int ns = row_dots_split(rows, len, fill);
   if (work_len < rows * ns) return fail(BSE_EINVAL, "row_dots: work buffer too small");
   hipLaunchKernelGGL(k_row_dots, dim3((unsigned)ns, (unsigned)rows), dim3(256), 0, st, A, B, len,
                      ns, work);
-  hipLaunchKernelGGL(k_row_dots_final, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, work,
-                     rows, ns, out);
+  hipLaunchKernelGGL(k_row_dots_final, dim3((unsigned)rows), dim3(64), 0, st, work, ns, out);
   CHECK_LAUNCH();
   return BSE_OK;
 }

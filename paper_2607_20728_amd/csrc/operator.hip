@@ -229,27 +229,35 @@ static int ensure_ov(bse_ctx* c, int nset) {
   return ctx_alloc_t(c, &c->Ov, need);
 }
 
-// GEMM with a context-owned split-K workspace
-int gemm(bse_ctx* c, int ta, int tb, long M, long N, long K, double alpha, const double* A,
-         long lda, const double* B, long ldb, double beta, double* C, long ldc) {
-  const long need = dgemm_work(M, N, K);
-  if (need > c->gw_len) {
-    ctx_release(c, c->gw);
-    c->gw = nullptr;
-    c->gw_len = 0;
-    BSE_TRY(ctx_alloc_t(c, &c->gw, (size_t)need));
-    c->gw_len = need;
-  }
-  return dgemm_ws(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, c->gw, c->gw_len, c->st);
+// the context-owned split-K workspace, at least `need` doubles; it grows by
+// more than was asked, so a solver's growing products do not replace it (and
+// drop the graphs that reference it) at every step
+int ensure_gw(bse_ctx* c, long need) {
+  if (need <= c->gw_len) return BSE_OK;
+  const long len = std::max(need, std::min(2 * c->gw_len, c->gw_len + (4L << 20)));
+  ctx_release(c, c->gw);
+  c->gw = nullptr;
+  c->gw_len = 0;
+  BSE_TRY(ctx_alloc_t(c, &c->gw, (size_t)len));
+  c->gw_len = len;
+  return BSE_OK;
 }
 
-int proj_c(bse_ctx* c, const double* X, double* Y, int nset) {
+// GEMM with a context-owned split-K workspace
+int gemm(bse_ctx* c, int ta, int tb, long M, long N, long K, double alpha, const double* A,
+         long lda, const double* B, long ldb, double beta, double* C, long ldc, bool fill) {
+  BSE_TRY(ensure_gw(c, dgemm_work(M, N, K, fill)));
+  return dgemm_ws(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, c->gw, c->gw_len, c->st,
+                  fill);
+}
+
+int proj_c(bse_ctx* c, const double* X, double* Y, int nset, bool fill) {
   if (nset <= 0) return BSE_OK;
   PhaseScope ps(c, PH_PROJ);
   BSE_TRY(ensure_ov(c, nset));
   const long npw = c->basis.npw, nv = c->nv, n = (long)nset * nv;
   // Ov[w][(s,v)] = <phi_w | x_{s,v}>
-  BSE_TRY(gemm(c, 0, 1, nv, n, npw, 1.0, c->Phi, npw, X, npw, 0.0, c->Ov, n));
+  BSE_TRY(gemm(c, 0, 1, nv, n, npw, 1.0, c->Phi, npw, X, npw, 0.0, c->Ov, n, fill));
   // Y = X - Ov^T Phi (the GEMM reads X as its C input: no copy when Y != X)
   BSE_TRY(dgemm_from(1, 0, n, npw, nv, -1.0, c->Ov, n, c->Phi, npw, 1.0, Y != X ? X : nullptr, Y,
                      npw, c->st));

@@ -36,16 +36,10 @@ int learned_features(bse_ctx* c, const double* U, std::vector<float>& F);
 int learned_eval(bse_ctx* c, const std::vector<float>& F, std::vector<double>& sigma,
                  std::vector<double>& gamma, bool* ok);
 
-int gram_tall(bse_ctx* c, const double* A, long m, const double* B, long n, long len, double* C) {
-  const long need = dgemm_tall_work(m, n, len);
-  if (need > c->gw_len) {
-    ctx_release(c, c->gw);
-    c->gw = nullptr;
-    c->gw_len = 0;
-    BSE_TRY(ctx_alloc_t(c, &c->gw, (size_t)need));
-    c->gw_len = need;
-  }
-  return dgemm_tall(m, n, len, 1.0, A, len, B, len, 0.0, C, n, c->gw, c->gw_len, c->st);
+int gram_tall(bse_ctx* c, const double* A, long m, const double* B, long n, long len, double* C,
+              bool fill) {
+  BSE_TRY(ensure_gw(c, dgemm_tall_work(m, n, len, fill)));
+  return dgemm_tall(m, n, len, 1.0, A, len, B, len, 0.0, C, n, c->gw, c->gw_len, c->st, fill);
 }
 
 namespace {
@@ -87,8 +81,8 @@ int copy_dev(bse_ctx* c, const double* s, double* d, size_t n) {
 }
 
 int dots_host(bse_ctx* c, const double* A, const double* B, long rows, long len, double* scratch,
-              std::vector<double>& out) {
-  const long need = row_dots_work(rows, len);
+              std::vector<double>& out, bool fill = true) {
+  const long need = row_dots_work(rows, len, fill);
   if (need > c->rdw_len) {
     ctx_release(c, c->rdw);
     c->rdw = nullptr;
@@ -96,7 +90,7 @@ int dots_host(bse_ctx* c, const double* A, const double* B, long rows, long len,
     BSE_TRY(ctx_alloc_t(c, &c->rdw, (size_t)need));
     c->rdw_len = need;
   }
-  BSE_TRY(row_dots(A, B, rows, len, scratch, c->rdw, c->rdw_len, c->st));
+  BSE_TRY(row_dots(A, B, rows, len, scratch, c->rdw, c->rdw_len, c->st, fill));
   out.resize(rows);
   return to_host(c, scratch, out, rows);
 }
@@ -178,8 +172,9 @@ int orth_block(bse_ctx* c, const double* V, long m, double* W, long k, long len,
   double* Cm = sm.p;                                     // [k][m]
   double* Bm = sm.p + (size_t)k * std::max(m, k);        // [k][k]
   double* vec = Bm + (size_t)k * k;                      // [2k]
+  const bool fill = m > 0;  // a starting block keeps its sums (dgemm_ws)
   std::vector<double> nrm;
-  if (dots_host(c, W, W, k, len, vec, nrm) != BSE_OK) return -BSE_EHIP;
+  if (dots_host(c, W, W, k, len, vec, nrm, fill) != BSE_OK) return -BSE_EHIP;
   std::vector<double> sc(k);
   for (long i = 0; i < k; ++i) sc[i] = nrm[i] > 0 ? 1.0 / std::sqrt(nrm[i]) : 0.0;
   if (to_dev(c, sc, vec, k) != BSE_OK) return -BSE_EHIP;
@@ -191,7 +186,7 @@ int orth_block(bse_ctx* c, const double* V, long m, double* W, long k, long len,
       if (dgemm(0, 0, kk, len, m, -1.0, Cm, m, V, len, 1.0, W, len, c->st) != BSE_OK)
         return -BSE_EHIP;
     }
-    if (gram_tall(c, W, kk, W, kk, len, Bm) != BSE_OK) return -BSE_EHIP;
+    if (gram_tall(c, W, kk, W, kk, len, Bm, fill) != BSE_OK) return -BSE_EHIP;
     std::vector<double> G((size_t)kk * kk), lam(kk);
     if (to_host(c, Bm, G, (size_t)kk * kk) != BSE_OK) return -BSE_EHIP;
     if (host_syev((int)kk, G.data(), lam.data())) return -fail(BSE_EINVAL, "Gram eigensolver failed");
@@ -230,7 +225,7 @@ static int chol_orth(bse_ctx* c, double* W, long k, long len, double* tmp) {
   double* Gd = sm.p;
   double* vec = sm.p + (size_t)k * k;
   std::vector<double> nrm;
-  if (dots_host(c, W, W, k, len, vec, nrm) != BSE_OK) return -BSE_EHIP;
+  if (dots_host(c, W, W, k, len, vec, nrm, false) != BSE_OK) return -BSE_EHIP;
   std::vector<double> sc(k);
   for (long i = 0; i < k; ++i) {
     if (!(nrm[i] > 0.0)) return 0;
@@ -240,7 +235,7 @@ static int chol_orth(bse_ctx* c, double* W, long k, long len, double* tmp) {
   if (row_scale(vec, W, k, len, c->st) != BSE_OK) return -BSE_EHIP;
   std::vector<double> G((size_t)k * k);
   for (int pass = 0; pass < 2; ++pass) {
-    if (gram_tall(c, W, k, W, k, len, Gd) != BSE_OK) return -BSE_EHIP;
+    if (gram_tall(c, W, k, W, k, len, Gd, false) != BSE_OK) return -BSE_EHIP;
     if (to_host(c, Gd, G, G.size()) != BSE_OK) return -BSE_EHIP;
     if (host_cholesky((int)k, G.data())) return 0;
     double lmin = G[0], lmax = G[0];
@@ -358,12 +353,12 @@ static int davidson_core(bse_ctx* c, int ns, const bse_solver_opts* o, double* o
       BSE_HIP(hipMemsetAsync(w, 0, sizeof(double) * L, c->st));
       BSE_TRY(to_dev(c, one, w + d[q].second, 1));
       ++q;
-      BSE_TRY(proj_c(c, w, w, 1));
-      BSE_TRY(dots_host(c, w, w, 1, L, vecd, nrm));
+      BSE_TRY(proj_c(c, w, w, 1, false));
+      BSE_TRY(dots_host(c, w, w, 1, L, vecd, nrm, false));
       if (std::sqrt(nrm[0]) > 0.3) ++k;
     }
   }
-  BSE_TRY(proj_c(c, W.p, W.p, k));
+  BSE_TRY(proj_c(c, W.p, W.p, k, false));
   int m = orth_block(c, V.p, 0, W.p, k, L, AW.p, 2, 1e-8);
   if (m <= 0) return m < 0 ? -m : fail(BSE_EINVAL, "Davidson: empty initial block");
   BSE_TRY(copy_dev(c, W.p, V.p, (size_t)m * L));
@@ -567,12 +562,12 @@ int full_bse(bse_ctx* c, int ns, const bse_solver_opts* o, double* omega, double
       BSE_HIP(hipMemsetAsync(w, 0, sizeof(double) * L, c->st));
       BSE_TRY(to_dev(c, one, w + d[q].second, 1));
       ++q;
-      BSE_TRY(proj_c(c, w, w, 1));
-      BSE_TRY(dots_host(c, w, w, 1, L, vecd, nrm));
+      BSE_TRY(proj_c(c, w, w, 1, false));
+      BSE_TRY(dots_host(c, w, w, 1, L, vecd, nrm, false));
       if (std::sqrt(nrm[0]) > 0.3) ++k;
     }
   }
-  BSE_TRY(proj_c(c, W.p, W.p, k));
+  BSE_TRY(proj_c(c, W.p, W.p, k, false));
   int m = 0;
   // orthonormalise kn new rows of W against the basis, apply A and B, append
   auto extend = [&](int kn) -> int {
@@ -1020,7 +1015,9 @@ int u_vector(bse_ctx* c, const double* Xs, double* U) {
   BSE_TRY(S.alloc((size_t)nv * nv));
   BSE_TRY(G.alloc((size_t)L));
   double* A = c->A_s;
-  BSE_TRY(proj_c(c, Xs, A, 1));
+  // (the pair densities of A may be held in FP32, where a last bit of A is one
+  // of theirs: its sums keep their chunks)
+  BSE_TRY(proj_c(c, Xs, A, 1, false));
   // a localised frame assembles U for A~ = U^T A with the localised
   // orbitals (its pruned W terms) and rotates the result back
   const double* Ak = A;
@@ -1033,7 +1030,7 @@ int u_vector(bse_ctx* c, const double* Xs, double* U) {
   BSE_TRY(to_grid(c, Ak, c->nv, 1, c->agrid));
   // kernel part before P_c, and S = <phi | K~ A>
   BSE_TRY(kernel_part(c, c->agrid, c->Zs));
-  BSE_TRY(dgemm(0, 1, nv, nv, npw, 1.0, Phik, npw, c->Zs, npw, 0.0, S.p, nv, c->st));
+  BSE_TRY(gemm(c, 0, 1, nv, nv, npw, 1.0, Phik, npw, c->Zs, npw, 0.0, S.p, nv));
   // g(r) = s (v_c*Drho) a - sum_v' sigma_{v'v} phi_v'  (drho holds v_c*Drho from kernel_part)
   double2* g1 = c->agrid + (long)c->nvh * nr;   // set 1: scratch
   const double2* y = nullptr;
@@ -1494,7 +1491,7 @@ int ground_state(bse_ctx* c, int n_want, double tol, bool warm) {
     if (k < 0) return -k;
     if (k < ns) return fail(BSE_EINVAL, "ground state: subspace collapsed (%d of %d)", k, ns);
     BSE_TRY(Happly(X.p, HX.p, 0.0));
-    BSE_TRY(gram_tall(c, X.p, nsl, HX.p, nsl, npw, Cd));
+    BSE_TRY(gram_tall(c, X.p, nsl, HX.p, nsl, npw, Cd, false));
     std::vector<double> Hs(nsl * nsl);
     BSE_TRY(to_host(c, Cd, Hs, Hs.size()));
     if (host_syev(ns, Hs.data(), theta.data())) return fail(BSE_EINVAL, "ground state: RR failed");
@@ -1521,7 +1518,7 @@ int ground_state(bse_ctx* c, int n_want, double tol, bool warm) {
     BSE_TRY(copy_dev(c, HX.p, Z.p, (size_t)n_want * npw));
     BSE_TRY(row_axpby(vec, X.p, nullptr, Z.p, n_want, npw, c->st));
     std::vector<double> r2;
-    BSE_TRY(dots_host(c, Z.p, Z.p, n_want, npw, vec, r2));
+    BSE_TRY(dots_host(c, Z.p, Z.p, n_want, npw, vec, r2, false));
     resid = 0;
     double resid_x = 0;  // the states above the occupied ones
     for (int i = 0; i < n_want; ++i) {
