@@ -451,19 +451,6 @@ __global__ __launch_bounds__(kPlaneThreads) void k_fft_plane_ct(cplx* data, Plan
 }
 
 // ---------------------------------------------------------------------------
-// Pruned sphere-plane transforms (compile-time lengths).  The sphere's modes
-// occupy rows |n2| <= m2 and columns |n3| <= m3 of a plane, so
-//  inverse (sphere -> plane): row transforms only on the 2 m2 + 1 rows that
-//    hold modes, kept in a compact block Q; then every column is transformed
-//    reading Q (zeros elsewhere) and its last pass writes the plane straight
-//    to memory, LB adjacent columns per batch (coalesced rows of LB values);
-//  forward (plane -> sphere): rows staged from memory in batches by
-//    coalesced copies and transformed, keeping only the 2 m3 + 1 columns that
-//    hold modes in Q; then those columns are transformed in place and the
-//    plane's modes gathered from Q.
-// Q holds (2 m2 + 1) x N3 or N2 x (2 m3 + 1) values instead of the whole
-// plane, so at 72 x 72 in FP64 two workgroups share a CU.
-// ---------------------------------------------------------------------------
 // one Stockham pass with functor access: element k of line l is read by
 // ld(k, l) and written by st(k, l, value)
 template <int R, int DIR, int N, int NS, int L, int NT, class LD, class ST>
@@ -522,178 +509,6 @@ __device__ __forceinline__ void fn_passes(LD ld, ST st, cplx* S0, cplx* S1, int 
   }
 }
 
-__device__ __forceinline__ int min_img(int i, int n) { return i < (n + 1) / 2 ? i : i - n; }
-
-// lines per batch of the pruned kernels: three candidates per precision for
-// the inverse pass, the first two for the forward pass (the launch scores
-// them, below)
-constexpr int kSphereLB[3] = {sizeof(cplx) == 16 ? 16 : 32, sizeof(cplx) == 16 ? 18 : 36,
-                              sizeof(cplx) == 16 ? 36 : 56};
-
-// LDS of the pruned kernels for sphere extents m2, m3 and batch LB
-template <int N2, int N3>
-size_t sphere_inv_lds(int m2, int lb) {
-  constexpr int nm = N2 > N3 ? N2 : N3;
-  return sizeof(cplx) * ((size_t)(2 * m2 + 1) * N3 + (size_t)plane_nscratch<N2, N3>() * nm * lb);
-}
-template <int N2, int N3>
-size_t sphere_fwd_whole_lds(int lb) {
-  constexpr int nm = N2 > N3 ? N2 : N3;
-  return sizeof(cplx) * ((size_t)N2 * N3 + (size_t)plane_nscratch<N2, N3>() * nm * lb);
-}
-template <int N2, int N3>
-size_t sphere_fwd_lds(int m3, int lb) {
-  constexpr int nm = N2 > N3 ? N2 : N3;
-  return sizeof(cplx) * ((size_t)N2 * (2 * m3 + 1) + (size_t)plane_nscratch<N2, N3>() * nm * lb +
-                         (size_t)lb * N3);
-}
-
-template <int N2, int N3, int DIR, int LB>
-__global__ __launch_bounds__(kPlaneThreads) void k_sphere_inv_ct(cplx* data, PlaneArgs pa,
-                                                                  AxisArgs ay, AxisArgs az) {
-  constexpr int NM = N2 > N3 ? N2 : N3;
-  constexpr int NT = kPlaneThreads;
-  static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
-  extern __shared__ cplx lds[];
-  const int m2 = pa.m2, K2 = 2 * pa.m2 + 1;
-  cplx* Q = lds;                       // [K2][N3]
-  cplx* S0 = Q + K2 * N3;
-  cplx* S1 = plane_nscratch<N2, N3>() == 2 ? S0 + NM * LB : S0;
-  // the planes of one grid share its coefficient rows: with pa.group they
-  // run on one XCD and read those rows into one L2
-  long g;
-  int pl;
-  xcd_item(blockIdx.x, pa.nplanes, pa.group != 0, g, pl);
-  if (g >= pa.batch) return;
-  const int i1 = pa.plane_i1[pl];
-  cplx* gp = data + g * pa.nr + (long)i1 * (N2 * N3);
-  for (int e = threadIdx.x; e < K2 * N3; e += NT) Q[e] = mk(0.0, 0.0);
-  __syncthreads();
-  {
-    const long set = g / pa.nvh;
-    const int p = (int)(g % pa.nvh);
-    const double* x1 = pa.X + (set * pa.nv + 2 * p) * (long)pa.npw;
-    const double* x2 = (2 * p + 1 < pa.nv) ? x1 + pa.npw : nullptr;
-    for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT) {
-      const int code = pa.ent_code[e];
-      cplx h;
-      if (code == 0) {
-        h = mk(x1[0] * pa.s0, x2 ? x2[0] * pa.s0 : 0.0);
-      } else {
-        const int k = abs(code) - 1;
-        const double c1 = x1[1 + 2 * k], q1 = x1[2 + 2 * k];
-        const double c2 = x2 ? x2[1 + 2 * k] : 0.0, q2 = x2 ? x2[2 + 2 * k] : 0.0;
-        h = code > 0 ? mk((c1 + q2) * pa.s1, (c2 - q1) * pa.s1)
-                     : mk((c1 - q2) * pa.s1, (q1 + c2) * pa.s1);
-      }
-      const int pos = pa.ent_pos[e];
-      const int q = min_img(pos / N3, N2) + m2;
-      Q[q * N3 + pos % N3] = h;
-    }
-  }
-  __syncthreads();
-  // rows holding modes (axis 3), in place in Q
-#pragma unroll 1
-  for (int l0 = 0; l0 < K2; l0 += LB)
-    ct_passes<N3, DIR, LB, NT, 0, 1, 1, N3, 1, N3>(Q + l0 * N3, S0, S1, Q + l0 * N3,
-                                                  min(LB, K2 - l0), az.tw);
-  // every column (axis 2) from Q, zeros outside its rows; the last pass
-  // writes the plane
-#pragma unroll 1
-  for (int l0 = 0; l0 < N3; l0 += LB) {
-    auto ld = [=](int k, int l) -> cplx {
-      const int q = min_img(k, N2) + m2;
-      return (q >= 0 && q < K2) ? Q[q * N3 + l0 + l] : mk(0.0, 0.0);
-    };
-    auto st = [=](int k, int l, cplx v) { gp[k * N3 + l0 + l] = v; };
-    fn_passes<N2, DIR, LB, NT, 0, 1>(ld, st, S0, S1, min(LB, N3 - l0), ay.tw);
-  }
-}
-
-template <int N2, int N3, int DIR, int LB>
-__global__ __launch_bounds__(kPlaneThreads) void k_sphere_fwd_ct(cplx* data, PlaneArgs pa,
-                                                                  AxisArgs ay, AxisArgs az) {
-  constexpr int NM = N2 > N3 ? N2 : N3;
-  constexpr int NT = kPlaneThreads;
-  static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
-  extern __shared__ cplx lds[];
-  const int m3 = pa.m3, K3 = 2 * pa.m3 + 1;
-  cplx* Q = lds;                       // [N2][K3]
-  cplx* S0 = Q + N2 * K3;
-  cplx* S1 = plane_nscratch<N2, N3>() == 2 ? S0 + NM * LB : S0;
-  cplx* R0 = S0 + plane_nscratch<N2, N3>() * NM * LB;  // staged rows [LB][N3]
-  const long g = blockIdx.x / pa.nplanes;
-  const int pl = (int)(blockIdx.x % pa.nplanes);
-  const int i1 = pa.plane_i1[pl];
-  const cplx* gp = data + g * pa.nr + (long)i1 * (N2 * N3);
-  // rows (axis 3): staged by coalesced copies, only the columns holding
-  // modes kept
-#pragma unroll 1
-  for (int l0 = 0; l0 < N2; l0 += LB) {
-    const int nl = min(LB, N2 - l0);
-    for (int e = threadIdx.x; e < nl * N3; e += NT) R0[e] = gp[l0 * N3 + e];
-    __syncthreads();
-    auto ld = [=](int k, int l) { return R0[l * N3 + k]; };
-    auto st = [=](int k, int l, cplx v) {
-      const int q = min_img(k, N3) + m3;
-      if (q >= 0 && q < K3) Q[(l0 + l) * K3 + q] = v;
-    };
-    fn_passes<N3, DIR, LB, NT, 0, 1>(ld, st, S0, S1, nl, az.tw);
-  }
-  // the kept columns (axis 2), in place in Q
-#pragma unroll 1
-  for (int l0 = 0; l0 < K3; l0 += LB) {
-    auto ld = [=](int k, int l) { return Q[k * K3 + l0 + l]; };
-    auto st = [=](int k, int l, cplx v) { Q[k * K3 + l0 + l] = v; };
-    fn_passes<N2, DIR, LB, NT, 0, 1>(ld, st, S0, S1, min(LB, K3 - l0), ay.tw);
-  }
-  cplx* cg = pa.compact + g * (long)pa.nent;
-  for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT) {
-    const int pos = pa.ent_pos[e];
-    cg[e] = Q[(pos / N3) * K3 + min_img(pos % N3, N3) + m3];
-  }
-}
-
-// The forward pass with the whole plane in LDS (one coalesced load of all
-// rows, row transforms in place), then only the 2 m3 + 1 columns that hold
-// modes transformed in place: for planes whose LDS fits two workgroups per
-// CU this beats staging rows in batches.
-template <int N2, int N3, int DIR, int LB>
-__global__ __launch_bounds__(kPlaneThreads) void k_sphere_fwd_whole(cplx* data, PlaneArgs pa,
-                                                                     AxisArgs ay, AxisArgs az) {
-  constexpr int NP2 = N2 * N3;
-  constexpr int NM = N2 > N3 ? N2 : N3;
-  constexpr int NT = kPlaneThreads;
-  static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
-  extern __shared__ cplx lds[];
-  const int m3 = pa.m3, K3 = 2 * pa.m3 + 1;
-  cplx* P = lds;
-  cplx* S0 = P + NP2;
-  cplx* S1 = plane_nscratch<N2, N3>() == 2 ? S0 + NM * LB : S0;
-  const long g = blockIdx.x / pa.nplanes;
-  const int pl = (int)(blockIdx.x % pa.nplanes);
-  const int i1 = pa.plane_i1[pl];
-  const cplx* gp = data + g * pa.nr + (long)i1 * NP2;
-#pragma unroll 4
-  for (int e = threadIdx.x; e < NP2; e += NT) P[e] = gp[e];
-  __syncthreads();
-#pragma unroll 1
-  for (int l0 = 0; l0 < N2; l0 += LB)
-    ct_passes<N3, DIR, LB, NT, 0, 1, 1, N3, 1, N3>(P + l0 * N3, S0, S1, P + l0 * N3,
-                                                  min(LB, N2 - l0), az.tw);
-  // column l of the kept set is n3 = l - m3, stored at index (l - m3) mod N3
-#pragma unroll 1
-  for (int l0 = 0; l0 < K3; l0 += LB) {
-    auto col = [=](int l) { const int n = l0 + l - m3; return n < 0 ? n + N3 : n; };
-    auto ld = [=](int k, int l) { return P[k * N3 + col(l)]; };
-    auto st = [=](int k, int l, cplx v) { P[k * N3 + col(l)] = v; };
-    fn_passes<N2, DIR, LB, NT, 0, 1>(ld, st, S0, S1, min(LB, K3 - l0), ay.tw);
-  }
-  cplx* cg = pa.compact + g * (long)pa.nent;
-  for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT)
-    cg[e] = P[pa.ent_pos[e]];
-}
-
 // ---------------------------------------------------------------------------
 // The plane part of a W solve in one visit: forward transform of both
 // in-plane axes, times f(G) s, plus the PDEP part on the sphere's modes
@@ -732,10 +547,27 @@ constexpr int wp_nt() {
   return t > 768 ? 768 : t;
 }
 
-// one Stockham pass of radix R over NL lines, in place: aux(k, l) is read
-// early for every output and handed to put(k, l, value, aux)
-template <int R, int DIR, int N, int NS, int NL, int NT, class GET, class AUX, class PUT>
-__device__ __forceinline__ void pass_inplace(GET get, AUX aux, PUT put,
+// line and butterfly of task u of nl lines (nl a constant, or NlDiv with the
+// reciprocal that makes u / nl one multiply: exact for u, nl < 2^16)
+template <int NL>
+struct NlAll {
+  static __device__ __forceinline__ int n() { return NL; }
+  static __device__ __forceinline__ int div(int u) { return u / NL; }
+};
+struct NlSome {
+  int nl;
+  unsigned inv;
+  __device__ __forceinline__ explicit NlSome(int n_) : nl(n_), inv(0xffffffffu / (unsigned)n_ + 1) {}
+  __device__ __forceinline__ int n() const { return nl; }
+  __device__ __forceinline__ int div(int u) const {  // (inv wraps to 0 for one line)
+    return nl == 1 ? u : (int)__umulhi((unsigned)u, inv);
+  }
+};
+
+// one Stockham pass of radix R over nl.n() of up to NL lines, in place:
+// aux(k, l) is read early for every output and handed to put(k, l, value, aux)
+template <int R, int DIR, int N, int NS, int NL, int NT, class NLS, class GET, class AUX, class PUT>
+__device__ __forceinline__ void pass_inplace(NLS nl, GET get, AUX aux, PUT put,
                                              const cplx* __restrict__ tw) {
   constexpr int NQ = N / R, TS = N / (NS * R);
   constexpr int TASKS = NQ * NL, MT = (TASKS + NT - 1) / NT;
@@ -745,8 +577,8 @@ __device__ __forceinline__ void pass_inplace(GET get, AUX aux, PUT put,
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     const int u = threadIdx.x + t * NT;
-    if (TASKS % NT == 0 || u < TASKS) {
-      const int l = u % NL, j = u / NL, k = j % NS;
+    if (u < NQ * nl.n()) {
+      const int j = nl.div(u), l = u - j * nl.n(), k = j % NS;
       const int base = (j / NS) * NS * R + k;
 #pragma unroll
       for (int r = 0; r < R; ++r) ax[t][r] = aux(base + r * NS, l);
@@ -772,8 +604,8 @@ __device__ __forceinline__ void pass_inplace(GET get, AUX aux, PUT put,
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     const int u = threadIdx.x + t * NT;
-    if (TASKS % NT == 0 || u < TASKS) {
-      const int l = u % NL, j = u / NL, k = j % NS;
+    if (u < NQ * nl.n()) {
+      const int j = nl.div(u), l = u - j * nl.n(), k = j % NS;
       const int base = (j / NS) * NS * R + k;
 #pragma unroll
       for (int r = 0; r < R; ++r) put(base + r * NS, l, v[t][r], ax[t][r]);
@@ -783,18 +615,18 @@ __device__ __forceinline__ void pass_inplace(GET get, AUX aux, PUT put,
 
 // all passes of NL lines of length N held in LDS (element k of line l is
 // *at(k, l)); the last pass leaves through put with aux
-template <int N, int DIR, int NL, int NT, int P, int NS, class AT, class AUX, class PUT>
-__device__ __forceinline__ void lines_inplace(AT at, AUX aux, PUT put, const cplx* tw) {
+template <int N, int DIR, int NL, int NT, int P, int NS, class NLS, class AT, class AUX, class PUT>
+__device__ __forceinline__ void lines_inplace(NLS nl, AT at, AUX aux, PUT put, const cplx* tw) {
   constexpr Fac F = factor(N);
   constexpr int R = F.r[P];
   auto get = [=](int k, int l) { return *at(k, l); };
   if constexpr (P == F.n - 1) {
-    pass_inplace<R, DIR, N, NS, NL, NT>(get, aux, put, tw);
+    pass_inplace<R, DIR, N, NS, NL, NT>(nl, get, aux, put, tw);
   } else {
     pass_inplace<R, DIR, N, NS, NL, NT>(
-        get, [](int, int) { return 0; }, [=](int k, int l, cplx v, int) { *at(k, l) = v; }, tw);
+        nl, get, [](int, int) { return 0; }, [=](int k, int l, cplx v, int) { *at(k, l) = v; }, tw);
     __syncthreads();
-    lines_inplace<N, DIR, NL, NT, P + 1, NS * R>(at, aux, put, tw);
+    lines_inplace<N, DIR, NL, NT, P + 1, NS * R>(nl, at, aux, put, tw);
   }
 }
 
@@ -830,13 +662,11 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N
 #pragma unroll 4
     for (int e = threadIdx.x; e < NP2; e += NT) P[e / N3 * RS + e % N3] = gp[e];
     __syncthreads();
-    lines_inplace<N3, -1, N2, NT, 0, 1>(
-        row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+    lines_inplace<N3, -1, N2, NT, 0, 1>(NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
     __syncthreads();
     const real* f = wa.f + (long)i1 * NP2;
     const real s = wa.s;
-    lines_inplace<N2, -1, N3, NT, 0, 1>(
-        col, [=](int k, int l) { return f[k * N3 + l]; },
+    lines_inplace<N2, -1, N3, NT, 0, 1>(NlAll<N3>(), col, [=](int k, int l) { return f[k * N3 + l]; },
         [=](int k, int l, cplx v, real m) {
           m *= s;
           v.x *= m;
@@ -871,11 +701,106 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N
     }
     __syncthreads();
   }
-  lines_inplace<N3, 1, N2, NT, 0, 1>(
-      row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+  lines_inplace<N3, 1, N2, NT, 0, 1>(NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
   __syncthreads();
+  lines_inplace<N2, 1, N3, NT, 0, 1>(NlAll<N3>(), col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
+}
+
+// ---------------------------------------------------------------------------
+// Pruned sphere-plane transforms.  The sphere's modes occupy rows |n2| <= m2
+// and columns |n3| <= m3 of a plane; the inverse transforms only those rows
+// and then every column, the forward every row and then only those columns.
+// A pass's tasks are packed, so no wave runs for the lines left out.
+// ---------------------------------------------------------------------------
+// Forward, in place as above: all rows, the columns that hold modes, and the
+// modes to the compact rows.
+// Bound by its passes and their barriers.  With scratch lines beside the
+// plane, fewer workgroups fitted a CU and the passes had bank conflicts: 6,720
+// FP32 grids of 48 x 48 x 120 took 11.9 ms, now 5.8; 10,400 FP64 grids of 64^3
+// 11.4, now 6.9 (3.9 TB/s).
+template <int N2, int N3>
+__global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_fwd_ip(const cplx* data, PlaneArgs pa,
+                                                                    const cplx* __restrict__ tw2,
+                                                                    const cplx* __restrict__ tw3) {
+  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = wp_nt<N2, N3>();
+  static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
+  extern __shared__ cplx lds[];
+  cplx* P = lds;
+  const long g = blockIdx.x / pa.nplanes;
+  const int pl = (int)(blockIdx.x % pa.nplanes);
+  const cplx* gp = data + g * pa.nr + (long)pa.plane_i1[pl] * NP2;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < NP2; e += NT) P[e / N3 * RS + e % N3] = gp[e];
+  __syncthreads();
+  auto none = [](int, int) { return 0; };
+  auto row = [=](int k, int l) { return P + l * RS + k; };
+  lines_inplace<N3, -1, N2, NT, 0, 1>(
+      NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+  __syncthreads();
+  // column l of the kept set is n3 = l - m3
+  const int m3 = pa.m3;
+  auto col = [=](int k, int l) { return P + k * RS + (l < m3 ? l - m3 + N3 : l - m3); };
+  lines_inplace<N2, -1, N3, NT, 0, 1>(
+      NlSome(2 * m3 + 1), col, none, [=](int k, int l, cplx v, int) { *col(k, l) = v; }, tw2);
+  __syncthreads();
+  cplx* cg = pa.compact + g * (long)pa.nent;
+  for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT) {
+    const int pos = pa.ent_pos[e];
+    cg[e] = P[pos / N3 * RS + pos % N3];
+  }
+}
+
+// Inverse, in place: the modes scattered into a cleared plane, the rows that
+// hold some, then all columns, whose last pass writes the plane to memory.
+// 800 FP64 grids of 64^3: 0.84 ms with scratch lines beside a compact block,
+// now 0.69; 720 FP32 grids of 48^3: 0.27 and 0.21; 1,024 FP64 grids of 72^3,
+// one workgroup per CU instead of two: 1.01 and 1.13.
+template <int N2, int N3>
+__global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data, PlaneArgs pa,
+                                                                    const cplx* __restrict__ tw2,
+                                                                    const cplx* __restrict__ tw3) {
+  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = wp_nt<N2, N3>();
+  extern __shared__ cplx lds[];
+  cplx* P = lds;
+  long g;
+  int pl;
+  xcd_item(blockIdx.x, pa.nplanes, pa.group != 0, g, pl);
+  if (g >= pa.batch) return;
+  cplx* gp = data + g * pa.nr + (long)pa.plane_i1[pl] * NP2;
+  for (int e = threadIdx.x; e < N2 * RS; e += NT) P[e] = mk(0.0, 0.0);
+  __syncthreads();
+  {
+    const long set = g / pa.nvh;
+    const int p = (int)(g % pa.nvh);
+    const double* x1 = pa.X + (set * pa.nv + 2 * p) * (long)pa.npw;
+    const double* x2 = (2 * p + 1 < pa.nv) ? x1 + pa.npw : nullptr;
+    for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT) {
+      const int code = pa.ent_code[e];
+      cplx h;
+      if (code == 0) {
+        h = mk(x1[0] * pa.s0, x2 ? x2[0] * pa.s0 : 0.0);
+      } else {
+        const int k = abs(code) - 1;
+        const double c1 = x1[1 + 2 * k], q1 = x1[2 + 2 * k];
+        const double c2 = x2 ? x2[1 + 2 * k] : 0.0, q2 = x2 ? x2[2 + 2 * k] : 0.0;
+        h = code > 0 ? mk((c1 + q2) * pa.s1, (c2 - q1) * pa.s1)
+                     : mk((c1 - q2) * pa.s1, (q1 + c2) * pa.s1);
+      }
+      const int pos = pa.ent_pos[e];
+      P[pos / N3 * RS + pos % N3] = h;
+    }
+  }
+  __syncthreads();
+  auto none = [](int, int) { return 0; };
+  // row l of the kept set is n2 = l - m2
+  const int m2 = pa.m2;
+  auto row = [=](int k, int l) { return P + (l < m2 ? l - m2 + N2 : l - m2) * RS + k; };
+  lines_inplace<N3, 1, N2, NT, 0, 1>(
+      NlSome(2 * m2 + 1), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+  __syncthreads();
+  auto col = [=](int k, int l) { return P + k * RS + l; };
   lines_inplace<N2, 1, N3, NT, 0, 1>(
-      col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
+      NlAll<N3>(), col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
 }
 
 template <int N>
@@ -1380,84 +1305,20 @@ int set_ct_lds_limits(int n2, int n3, int n1) {
   return BSE_OK;
 }
 
-// padded lines of the pruned kernels' batches (same line counts as below)
-inline long sphere_padded(int nrow, int ncol, int lb) {
-  return (long)((nrow + lb - 1) / lb + (ncol + lb - 1) / lb) * lb;
-}
-// rounds of butterflies (at most one per thread each) of the line
-// transforms of length n in batches of lb lines
-inline long pass_rounds(int n, int lb) {
-  const Fac f = factor(n);
-  long r = 0;
-  for (int p = 0; p < f.n; ++p) r += ((long)(n / f.r[p]) * lb + kPlaneThreads - 1) / kPlaneThreads;
-  return r;
-}
-// rounds of the pruned kernels: nrow row transforms of length lrow, then
-// ncol column transforms of length lcol (inverse: K2 rows of N3, N3 columns
-// of N2; forward: N2 rows of N3, K3 columns of N2)
-inline long sphere_rounds(int nrow, int lrow, int ncol, int lcol, int lb) {
-  return (long)((nrow + lb - 1) / lb) * pass_rounds(lrow, lb) +
-         (long)((ncol + lb - 1) / lb) * pass_rounds(lcol, lb);
-}
-
 // pruned sphere-plane launches: false when the size has no compiled kernel
-// or the LDS the extents need exceeds the device's
-bool launch_sphere_ct(int n2, int n3, bool inverse, int m, size_t max_lds, dim3 grid,
-                      hipStream_t st, cplx* data, PlaneArgs pa, AxisArgs ay, AxisArgs az) {
-  // inverse pass: batch size k in {0, 1, 2}, scored by the rounds of
-  // butterflies over the workgroup's threads (each ending at a barrier),
-  // tripled when two workgroups do not fit a CU.  Forward pass: batch size k
-  // in {0, 1} and the staged (w = 0) or whole-plane (w = 1) kernel, scored by
-  // the padded line count, doubled when two workgroups do not fit a CU (the
-  // choices measured fastest at the grids in use).  Ties go to the
-  // whole-plane kernel and the smaller batch.
+// or the plane does not fit the device's LDS
+bool launch_sphere_ct(int n2, int n3, bool inverse, size_t max_lds, dim3 grid, hipStream_t st,
+                      cplx* data, PlaneArgs pa, AxisArgs ay, AxisArgs az) {
 #define C(A, B)                                                                               \
   if (n2 == A && n3 == B) {                                                                   \
-    int pick = -1, pw = 0;                                                                    \
-    long best = 0;                                                                            \
-    size_t shm = 0;                                                                           \
-    for (int w = inverse ? 0 : 1; w >= 0; --w)                                                \
-      for (int k = 0; k < (inverse ? 3 : 2); ++k) {                                           \
-        const int lb = kSphereLB[k];                                                          \
-        const size_t need = inverse ? sphere_inv_lds<A, B>(m, lb)                             \
-                            : w ? sphere_fwd_whole_lds<A, B>(lb) : sphere_fwd_lds<A, B>(m, lb); \
-        if (need > max_lds) continue;                                                         \
-        const long score = inverse                                                            \
-            ? sphere_rounds(2 * m + 1, B, B, A, lb) * (need <= 81920 ? 1 : 3)                 \
-            : sphere_padded(A, 2 * m + 1, lb) * (need <= 81920 ? 1 : 2);                      \
-        if (pick < 0 || score < best) {                                                       \
-          pick = k;                                                                           \
-          pw = w;                                                                             \
-          best = score;                                                                       \
-          shm = need;                                                                         \
-        }                                                                                     \
-      }                                                                                       \
-    if (pick < 0) return false;                                                               \
-    if (inverse) {                                                                            \
-      if (pick == 0)                                                                          \
-        hipLaunchKernelGGL((k_sphere_inv_ct<A, B, 1, kSphereLB[0]>), grid, dim3(kPlaneThreads), \
-                           shm, st, data, pa, ay, az);                                        \
-      else if (pick == 1)                                                                     \
-        hipLaunchKernelGGL((k_sphere_inv_ct<A, B, 1, kSphereLB[1]>), grid, dim3(kPlaneThreads), \
-                           shm, st, data, pa, ay, az);                                        \
-      else                                                                                    \
-        hipLaunchKernelGGL((k_sphere_inv_ct<A, B, 1, kSphereLB[2]>), grid, dim3(kPlaneThreads), \
-                           shm, st, data, pa, ay, az);                                        \
-    } else if (pw) {                                                                          \
-      if (pick == 0)                                                                          \
-        hipLaunchKernelGGL((k_sphere_fwd_whole<A, B, -1, kSphereLB[0]>), grid,                \
-                           dim3(kPlaneThreads), shm, st, data, pa, ay, az);                   \
-      else                                                                                    \
-        hipLaunchKernelGGL((k_sphere_fwd_whole<A, B, -1, kSphereLB[1]>), grid,                \
-                           dim3(kPlaneThreads), shm, st, data, pa, ay, az);                   \
-    } else {                                                                                  \
-      if (pick == 0)                                                                          \
-        hipLaunchKernelGGL((k_sphere_fwd_ct<A, B, -1, kSphereLB[0]>), grid,                   \
-                           dim3(kPlaneThreads), shm, st, data, pa, ay, az);                   \
-      else                                                                                    \
-        hipLaunchKernelGGL((k_sphere_fwd_ct<A, B, -1, kSphereLB[1]>), grid,                   \
-                           dim3(kPlaneThreads), shm, st, data, pa, ay, az);                   \
-    }                                                                                         \
+    constexpr size_t shm = wp_lds<A, B>();                                                    \
+    if (shm > max_lds) return false;                                                          \
+    if (inverse)                                                                              \
+      hipLaunchKernelGGL((k_sphere_inv_ip<A, B>), grid, dim3(wp_nt<A, B>()), shm, st, data, pa, \
+                         ay.tw, az.tw);                                                       \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_sphere_fwd_ip<A, B>), grid, dim3(wp_nt<A, B>()), shm, st, data, pa, \
+                         ay.tw, az.tw);                                                       \
     return true;                                                                              \
   }
   BSEX_PLANE_SIZES(C)
@@ -1465,19 +1326,13 @@ bool launch_sphere_ct(int n2, int n3, bool inverse, int m, size_t max_lds, dim3 
   return false;
 }
 
-// the pruned kernels may use up to the device's LDS (extents are known only
-// with a sphere)
+// the pruned kernels may use up to the device's LDS
 int set_sphere_lds_limits(int n2, int n3, size_t max_lds) {
 #define C(A, B)                                                                               \
   if (n2 == A && n3 == B) {                                                                   \
     const int lim = (int)max_lds;                                                             \
-    const void* fns[] = {(const void*)k_sphere_inv_ct<A, B, 1, kSphereLB[0]>,                 \
-                         (const void*)k_sphere_inv_ct<A, B, 1, kSphereLB[1]>,                 \
-                         (const void*)k_sphere_inv_ct<A, B, 1, kSphereLB[2]>,                 \
-                         (const void*)k_sphere_fwd_ct<A, B, -1, kSphereLB[0]>,                \
-                         (const void*)k_sphere_fwd_ct<A, B, -1, kSphereLB[1]>,                \
-                         (const void*)k_sphere_fwd_whole<A, B, -1, kSphereLB[0]>,             \
-                         (const void*)k_sphere_fwd_whole<A, B, -1, kSphereLB[1]>};            \
+    const void* fns[] = {(const void*)k_sphere_fwd_ip<A, B>,                                  \
+                         (const void*)k_sphere_inv_ip<A, B>};                                 \
     for (const void* f : fns)                                                                 \
       BSE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim));       \
   }
@@ -1592,9 +1447,8 @@ static bool launch_sphere(const FftPlan& p, const SpherePlan& sp, bool inverse, 
   pa.nr = p.nr;
   pa.m2 = sp.m2;
   pa.m3 = sp.m3;
-  return launch_sphere_ct(p.N[1], p.N[2], inverse, inverse ? sp.m2 : sp.m3, p.max_lds,
-                          dim3((unsigned)groups), st, data, pa, axis_args(p.ax[1]),
-                          axis_args(p.ax[2]));
+  return launch_sphere_ct(p.N[1], p.N[2], inverse, p.max_lds, dim3((unsigned)groups), st, data,
+                          pa, axis_args(p.ax[1]), axis_args(p.ax[2]));
 }
 
 int init_kernels(FftPlan* p) {
