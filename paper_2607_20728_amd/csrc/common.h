@@ -115,10 +115,13 @@ void sphere_plan_free(SpherePlan* sp);
 // grid[set][p] = sum_G f(G) e^{iGr} of orbitals 2p, 2p+1 of each set (packed),
 // f(0) = x0/sqrt(Omega), f(+-G) = (xc -+ i xs)/sqrt(2 Omega).  Planes that miss
 // the sphere are left unwritten by the first kernel and read as zero.
+// With a field f [nr] (where fwd_pairs_supported: the same axis kernels) the
+// grids end as the forward axis-1 pass of f(r) times those orbitals, on the
+// sphere's planes only: planes_to_compact then gives the sphere entries.
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
-                   int nset, double2* grid, hipStream_t st);
+                   int nset, double2* grid, hipStream_t st, const double* f = nullptr);
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
-                   int nset, float2* grid, hipStream_t st);
+                   int nset, float2* grid, hipStream_t st, const float* f = nullptr);
 // compact[g][e] = sum_r grid[g](r) e^{-i G_e.r} for the sphere entries e only
 // (the grid is overwritten).
 int grid_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,

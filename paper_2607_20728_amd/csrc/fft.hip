@@ -253,12 +253,12 @@ int fft3d_w_planes(const FftPlan& p, const SpherePlan& sp, float2* data, long ba
   return f32::fft3d_w_planes(p, sp, data, batch, f, s, X, Xf, nrow, omega, st);
 }
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
-                   int nset, double2* grid, hipStream_t st) {
-  return f64::sphere_to_grid(p, sp, omega, X, nv, nset, grid, st);
+                   int nset, double2* grid, hipStream_t st, const double* f) {
+  return f64::sphere_to_grid(p, sp, omega, X, nv, nset, grid, f, st);
 }
 int sphere_to_grid(const FftPlan& p, const SpherePlan& sp, double omega, const double* X, int nv,
-                   int nset, float2* grid, hipStream_t st) {
-  return f32::sphere_to_grid(p, sp, omega, X, nv, nset, grid, st);
+                   int nset, float2* grid, hipStream_t st, const float* f) {
+  return f32::sphere_to_grid(p, sp, omega, X, nv, nset, grid, f, st);
 }
 int grid_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,
                     double2* compact, hipStream_t st) {

@@ -280,14 +280,23 @@ static int ensure_compact(bse_ctx* c, long ngrids) {
   return BSE_OK;
 }
 
-int from_grid(bse_ctx* c, double2* grids, int nvs, int nset, const double* A, const double* eps,
-              double shift, double* Y) {
+// axis_done: the grids hold the forward axis-1 pass already
+static int from_grid(bse_ctx* c, double2* grids, int nvs, int nset, const double* A,
+                     const double* eps, double shift, double* Y, bool axis_done) {
   PhaseScope ps(c, PH_FFT_FWD);
   const long ng = (long)nset * ((nvs + 1) / 2);
   BSE_TRY(ensure_compact(c, ng));
-  BSE_TRY(grid_to_compact(c->fft, c->sp, grids, ng, c->compact, c->st));
+  if (axis_done)
+    BSE_TRY(planes_to_compact(c->fft, c->sp, grids, ng, c->compact, c->st));
+  else
+    BSE_TRY(grid_to_compact(c->fft, c->sp, grids, ng, c->compact, c->st));
   return gather_sets(c->cmap, c->compact, nvs, nset, 1.0 / (double)c->basis.nr, A, c->T, eps,
                      shift, 0.0, Y, c->st);
+}
+
+int from_grid(bse_ctx* c, double2* grids, int nvs, int nset, const double* A, const double* eps,
+              double shift, double* Y) {
+  return from_grid(c, grids, nvs, nset, A, eps, shift, Y, false);
 }
 
 // Y = (T + shift - eps_v) X + <e| V(r) x(r)> on nset sets of nvs orbitals
@@ -295,13 +304,18 @@ int from_grid(bse_ctx* c, double2* grids, int nvs, int nset, const double* A, co
 // by P_c (then nvs must be c->nv).
 int apply_H(bse_ctx* c, int nvs, int nset, const double* X, double* Y, double2* grids,
             double shift, const double* eps, int project) {
-  BSE_TRY(to_grid(c, X, nvs, nset, grids));
-  const long ng = (long)nset * ((nvs + 1) / 2);
-  {
+  // the potential's multiply inside the axis-1 passes where they have kernels
+  const bool fused = fwd_pairs_supported(c->fft, false);
+  if (fused) {
+    PhaseScope ps(c, PH_FFT_INV);
+    BSE_TRY(sphere_to_grid(c->fft, c->sp, c->basis.omega, X, nvs, nset, grids, c->st, c->Vr));
+  } else {
+    BSE_TRY(to_grid(c, X, nvs, nset, grids));
+    const long ng = (long)nset * ((nvs + 1) / 2);
     PhaseScope ps(c, PH_COMBINE);
     BSE_TRY(mul_real_field(grids, ng, c->basis.nr, c->Vr, 1.0, c->st));
   }
-  BSE_TRY(from_grid(c, grids, nvs, nset, X, eps, shift, Y));
+  BSE_TRY(from_grid(c, grids, nvs, nset, X, eps, shift, Y, fused));
   if (project) BSE_TRY(proj_c(c, Y, Y, nset));
   return BSE_OK;
 }
@@ -895,11 +909,14 @@ static int ensure_compact_f(bse_ctx* c, long ngrids) {
 }
 
 static int from_grid_f(bse_ctx* c, float2* grids, int nvs, int nset, const double* A,
-                       const double* eps, double shift, double* Y) {
+                       const double* eps, double shift, double* Y, bool axis_done = false) {
   PhaseScope ps(c, PH_FFT_FWD);
   const long ng = (long)nset * ((nvs + 1) / 2);
   BSE_TRY(ensure_compact_f(c, ng));
-  BSE_TRY(grid_to_compact(c->fft, c->sp, grids, ng, c->compact_f, c->st));
+  if (axis_done)
+    BSE_TRY(planes_to_compact(c->fft, c->sp, grids, ng, c->compact_f, c->st));
+  else
+    BSE_TRY(grid_to_compact(c->fft, c->sp, grids, ng, c->compact_f, c->st));
   return gather_sets(c->cmap, c->compact_f, nvs, nset, 1.0 / (double)c->basis.nr, A, c->T, eps,
                      shift, 0.0, Y, c->st);
 }
@@ -953,12 +970,14 @@ int apply_H_f(bse_ctx* c, int nvs, int nset, const double* X, double* Y, double 
               const double* eps, int project) {
   const long ng = (long)nset * ((nvs + 1) / 2);
   if (ng > (long)c->nbc_f * c->nvh) return fail(BSE_EINVAL, "FP32 grid work too small");
+  const bool fused = fwd_pairs_supported(c->fft, true);
   {
     PhaseScope ps(c, PH_FFT_INV);
-    BSE_TRY(sphere_to_grid(c->fft, c->sp, c->basis.omega, X, nvs, nset, c->agrid_f, c->st));
+    BSE_TRY(sphere_to_grid(c->fft, c->sp, c->basis.omega, X, nvs, nset, c->agrid_f, c->st,
+                           fused ? c->Vr_f : nullptr));
   }
-  BSE_TRY(mul_real_field(c->agrid_f, ng, c->basis.nr, c->Vr_f, 1.0f, c->st));
-  BSE_TRY(from_grid_f(c, c->agrid_f, nvs, nset, X, eps, shift, Y));
+  if (!fused) BSE_TRY(mul_real_field(c->agrid_f, ng, c->basis.nr, c->Vr_f, 1.0f, c->st));
+  BSE_TRY(from_grid_f(c, c->agrid_f, nvs, nset, X, eps, shift, Y, fused));
   if (project) BSE_TRY(proj_c(c, Y, Y, nset));
   return BSE_OK;
 }
