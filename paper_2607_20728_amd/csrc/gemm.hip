@@ -25,7 +25,13 @@ namespace {
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
-constexpr int BN = 64, BK = 16;
+constexpr int BN = 64;
+// K step: 1024 cycles of a wave's matrix work in a 64 x 64 tile
+template <typename T>
+constexpr int bk_full() {
+  return sizeof(T) == 8 ? 16 : 32;
+}
+constexpr int BK = bk_full<double>();
 
 // rows of the workgroup tile for an M-row output
 inline int bm_for(long M) { return M <= 16 ? 16 : 64; }
@@ -70,8 +76,12 @@ __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
   constexpr int WGN = 4 / WGM;           // waves along N
   constexpr int TM = BM / (16 * WGM);    // MFMA tiles per wave along M
   constexpr int TN = BN / (16 * WGN);    // and along N
-  __shared__ T As[BK][BM + 1];
-  __shared__ T Bs[BK][BN + 1];
+  // padded rows: 8-byte values need an odd stride, 4-byte ones one that keeps
+  // the four k rows of an operand read and the 32 of a write on banks apart
+  constexpr int PAD = sizeof(T) == 8 ? 1 : 17;
+  constexpr int NBUF = BK == BKF ? 1 : 2;
+  __shared__ T As[NBUF][BK][BM + PAD];
+  __shared__ T Bs[NBUF][BK][BN + PAD];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -96,7 +106,16 @@ __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
 
   // element e of a thread's share of the A tile is (m, k) = a_mk(e), of the
   // B tile (n, k) = b_nk(e); the next K step's tiles are loaded into
-  // registers while the matrix cores work on the current one
+  // registers while the matrix cores work on the current one.  Each element
+  // has a pointer that a step advances, and rows past the edge of op(A) or
+  // op(B) read the last one (their products reach no stored element), so only
+  // a last, partial K step tests anything: with an address and two tests per
+  // element and step, the vector units were busy for half as long as the
+  // matrix cores (FP32, 3,400 x 256 x 60,000: 2.07 ms, now 1.74; FP64, split
+  // 3,470 x 320 x 34,000: 1.33, now 1.22).  The FP64 form of few workgroups
+  // runs a few steps only and keeps the tests: setting up 16 pointers took
+  // longer (8.0 us against 7.4 for a product of one coupling column).
+  constexpr bool PTR = BK != BKF || sizeof(T) == 4;
   constexpr int NA = BM * BK / 256, NB = BN * BK / 256;
   auto a_mk = [&](int e, int& m, int& k) {
     if (TA) {  // A[k][m], m contiguous
@@ -117,66 +136,148 @@ __device__ __forceinline__ void gemm_tile(long M, long N, long K, T alpha,
     }
   };
   T ra[NA], rb[NB];
+  const T* pa[PTR ? NA : 1];
+  const T* pb[PTR ? NB : 1];
+#pragma unroll
+  for (int q = 0; PTR && q < NA; ++q) {
+    int m, k;
+    a_mk(tid + 256 * q, m, k);
+    const unsigned gm = (unsigned)min(m0 + m, M - 1);
+    pa[q] = TA ? A + (kb + k) * lda + gm : A + (unsigned long)gm * lda + kb + k;
+  }
+#pragma unroll
+  for (int q = 0; PTR && q < NB; ++q) {
+    int n, k;
+    b_nk(tid + 256 * q, n, k);
+    const unsigned gn = (unsigned)min(n0 + n, N - 1);
+    pb[q] = TB ? B + (unsigned long)gn * ldb + kb + k : B + (kb + k) * ldb + gn;
+  }
+  const long da = TA ? BK * lda : BK, db = TB ? BK : BK * ldb;
   auto fetch = [&](long k0) {
+    if constexpr (!PTR) {
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        int m, k;
+        a_mk(tid + 256 * q, m, k);
+        const long gm = m0 + m, gk = k0 + k;
+        ra[q] = (gm < M && gk < ke) ? (TA ? A[gk * lda + gm] : A[gm * lda + gk]) : (T)0;
+      }
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        int n, k;
+        b_nk(tid + 256 * q, n, k);
+        const long gn = n0 + n, gk = k0 + k;
+        rb[q] = (gn < N && gk < ke) ? (TB ? B[gn * ldb + gk] : B[gk * ldb + gn]) : (T)0;
+      }
+      return;
+    }
+    if (k0 + BK <= ke) {
+#pragma unroll
+      for (int q = 0; q < NA; ++q) ra[q] = *pa[q];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) rb[q] = *pb[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        int m, k;
+        a_mk(tid + 256 * q, m, k);
+        ra[q] = k0 + k < ke ? *pa[q] : (T)0;
+      }
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        int n, k;
+        b_nk(tid + 256 * q, n, k);
+        rb[q] = k0 + k < ke ? *pb[q] : (T)0;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NA; ++q) pa[q] += da;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) pb[q] += db;
+  };
+  auto stage = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
       int m, k;
       a_mk(tid + 256 * q, m, k);
-      const long gm = m0 + m, gk = k0 + k;
-      ra[q] = (gm < M && gk < ke) ? (TA ? A[gk * lda + gm] : A[gm * lda + gk]) : (T)0;
+      As[buf][k][m] = ra[q];
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       int n, k;
       b_nk(tid + 256 * q, n, k);
-      const long gn = n0 + n, gk = k0 + k;
-      rb[q] = (gn < N && gk < ke) ? (TB ? B[gn * ldb + gk] : B[gk * ldb + gn]) : (T)0;
+      Bs[buf][k][n] = rb[q];
     }
   };
-  if (kb < ke) fetch(kb);
-  for (long k0 = kb; k0 < ke; k0 += BK) {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      int m, k;
-      a_mk(tid + 256 * q, m, k);
-      As[k][m] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      int n, k;
-      b_nk(tid + 256 * q, n, k);
-      Bs[k][n] = rb[q];
-    }
-    __syncthreads();
-    if (k0 + BK < ke) fetch(k0 + BK);
+  auto multiply = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
       const int kr = kk + (lane >> 4);
       T a[TM], b[TN];
 #pragma unroll
-      for (int t = 0; t < TM; ++t) a[t] = As[kr][wm * 16 * TM + t * 16 + (lane & 15)];
+      for (int t = 0; t < TM; ++t) a[t] = As[buf][kr][wm * 16 * TM + t * 16 + (lane & 15)];
 #pragma unroll
-      for (int t = 0; t < TN; ++t) b[t] = Bs[kr][wn * 16 * TN + t * 16 + (lane & 15)];
+      for (int t = 0; t < TN; ++t) b[t] = Bs[buf][kr][wn * 16 * TN + t * 16 + (lane & 15)];
 #pragma unroll
       for (int ta = 0; ta < TM; ++ta)
 #pragma unroll
         for (int tb = 0; tb < TN; ++tb)
           acc[ta][tb] = MF::step(a[ta], b[tb], acc[ta][tb]);
     }
-    __syncthreads();
+  };
+  if (kb < ke) {
+    fetch(kb);
+    if constexpr (NBUF == 2) {
+      // one barrier a step: the next tiles go to the other buffer
+      stage(0);
+      if (kb + BK < ke) fetch(kb + BK);
+      __syncthreads();
+      int buf = 0;
+      for (long k0 = kb; k0 < ke; k0 += BK, buf ^= 1) {
+        multiply(buf);
+        if (k0 + BK < ke) {
+          stage(buf ^ 1);
+          if (k0 + 2 * BK < ke) fetch(k0 + 2 * BK);
+        }
+        __syncthreads();
+      }
+    } else {
+      for (long k0 = kb; k0 < ke; k0 += BK) {
+        stage(0);
+        __syncthreads();
+        if (k0 + BK < ke) fetch(k0 + BK);
+        multiply(0);
+        __syncthreads();
+      }
+    }
   }
+  // the beta term's values are read together: one at a time, each between two
+  // stores that may alias it, they took the latency of 16 reads in a row
   T* Cz = C + (long)blockIdx.z * c_split_stride;
+  const long cm = m0 + wm * 16 * TM, cn = n0 + wn * 16 * TN + (lane & 15);
+  T old[TM][TN][4];
+  if (beta != (T)0) {
+    const T* Co = Cin ? Cin : Cz;
+#pragma unroll
+    for (int ta = 0; ta < TM; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < TN; ++tb)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const long gm = cm + ta * 16 + MF::row(lane >> 4, t), gn = cn + tb * 16;
+          old[ta][tb][t] = gm < M && gn < N ? Co[gm * ldc + gn] : (T)0;
+        }
+  }
 #pragma unroll
   for (int ta = 0; ta < TM; ++ta)
 #pragma unroll
     for (int tb = 0; tb < TN; ++tb)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const long gm = m0 + wm * 16 * TM + ta * 16 + MF::row(lane >> 4, t);
-        const long gn = n0 + wn * 16 * TN + tb * 16 + (lane & 15);
+        const long gm = cm + ta * 16 + MF::row(lane >> 4, t), gn = cn + tb * 16;
         if (gm < M && gn < N) {
           T v = alpha * acc[ta][tb][t];
-          if (beta != (T)0) v += beta * (Cin ? Cin[gm * ldc + gn] : Cz[gm * ldc + gn]);
+          if (beta != (T)0) v += beta * old[ta][tb][t];
           Cz[gm * ldc + gn] = v;
         }
       }
@@ -295,10 +396,10 @@ template <typename T, int TA, int TB, typename... Args>
 void launch_form(const Tiling& t, dim3 grid, hipStream_t st, Args... args) {
   if (t.bm == 16)
     t.bk == BKF ? launch_tile<T, TA, TB, 16, BN, BKF>(grid, st, args...)
-                : launch_tile<T, TA, TB, 16, BN, BK>(grid, st, args...);
+                : launch_tile<T, TA, TB, 16, BN, bk_full<T>()>(grid, st, args...);
   else
     t.bk == BKF ? launch_tile<T, TA, TB, BMF, BMF, BKF>(grid, st, args...)
-                : launch_tile<T, TA, TB, 64, BN, BK>(grid, st, args...);
+                : launch_tile<T, TA, TB, 64, BN, bk_full<T>()>(grid, st, args...);
 }
 
 // few: below this many workgroups the latency forms serve.  FP64 fills a
@@ -311,7 +412,7 @@ int launch(int ta, int tb, long M, long N, long K, T alpha, const T* A, long lda
   const Tiling t = tiling(M, N, K, s, sizeof(T) == 8 ? 256 : 512);
   const int by_row = t.nt < t.mt && xcd_group_on() ? 1 : 0;
   const long nwg = (by_row ? round8(t.mt) : t.mt) * t.nt;
-  if (nwg > 0x7fffffffL || s > 65535) return fail(BSE_EINVAL, "gemm: output too large for the grid");
+  if (nwg > 0x7fffffffL || M > 0xffffffffL || N > 0xffffffffL || s > 65535) return fail(BSE_EINVAL, "gemm: output too large for the grid");
   const dim3 grid((unsigned)nwg, 1, (unsigned)s);
   const int ntn = (int)t.nt;
 #define GO(TA_, TB_)                                                                             \
