@@ -159,39 +159,47 @@ __global__ void k_real_part(const double2* __restrict__ g, long nr, double* __re
   for (long e = gtid(); e < nr; e += gstride()) out[e] = g[e].x;
 }
 
-// A thread owns one grid point and a group of up to TD_B vectors, so each
-// phi_v(r) is read once per group rather than once per pair of vectors.
-constexpr int TD_B = 8;
-
-template <typename V2, typename R>
-__global__ void k_transition_density(const V2* __restrict__ phir, const V2* __restrict__ a,
-                                     int nvh, int nb, long nr, V2* __restrict__ drho) {
-  const long ngroups = (nb + TD_B - 1) / TD_B;
-  for (long e = gtid(); e < ngroups * nr; e += gstride()) {
-    const long r = e % nr;
-    const int b0 = (int)(e / nr) * TD_B;
-    const int nbg = min(TD_B, nb - b0);
-    R s[TD_B];
+// A thread owns one grid point and a group of up to TB vectors (grid (points,
+// groups)), so each phi_v(r) is read once per group rather than once per pair
+// of vectors.  Bound by HBM on a large grid.  A small one leaves too few waves
+// in flight at 8 vectors a thread, and takes 2 (1 for a single vector), phi
+// then coming from L2; four orbital pairs are loaded at a time.  Vectors past
+// the last are read as it, so the loads need no branch.
+template <typename V2, typename R, int TB>
+__global__ __launch_bounds__(256) void k_transition_density(const V2* __restrict__ phir,
+                                                            const V2* __restrict__ a, int nvh,
+                                                            int nb, long nr,
+                                                            V2* __restrict__ drho) {
+  constexpr int PB = TB == 8 ? 2 : 4;
+  const long r = (long)blockIdx.x * 256 + threadIdx.x;
+  if (r >= nr) return;
+  const int b0 = blockIdx.y * TB;
+  const int nbg = min(TB, nb - b0);
+  const V2* x[TB];
+  R s[TB];
 #pragma unroll
-    for (int o = 0; o < TD_B; ++o) s[o] = 0;
-    for (int p = 0; p < nvh; ++p) {
-      const V2 f = phir[(long)p * nr + r];
+  for (int o = 0; o < TB; ++o) {
+    x[o] = a + (long)(b0 + min(o, nbg - 1)) * nvh * nr + r;
+    s[o] = 0;
+  }
+  const V2* fp = phir + r;
+#pragma unroll PB
+  for (int p = 0; p < nvh; ++p) {
+    const long e = (long)p * nr;
+    const V2 f = fp[e];
 #pragma unroll
-      for (int o = 0; o < TD_B; ++o) {
-        if (o < nbg) {
-          const V2 x = a[((long)(b0 + o) * nvh + p) * nr + r];
-          s[o] += f.x * x.x + f.y * x.y;
-        }
-      }
+    for (int o = 0; o < TB; ++o) {
+      const V2 v = x[o][e];
+      s[o] += f.x * v.x + f.y * v.y;
     }
+  }
 #pragma unroll
-    for (int o = 0; o < TD_B; o += 2) {
-      if (o < nbg) {
-        V2 out;
-        out.x = s[o];
-        out.y = (o + 1 < nbg) ? s[o + 1] : (R)0;
-        drho[(long)((b0 + o) / 2) * nr + r] = out;
-      }
+  for (int o = 0; o < TB; o += 2) {
+    if (o < nbg) {
+      V2 out;
+      out.x = s[o];
+      out.y = (o + 1 < nbg) ? s[(o + 1) % TB] : (R)0;
+      drho[(long)((b0 + o) / 2) * nr + r] = out;
     }
   }
 }
@@ -1183,24 +1191,40 @@ int real_part(const double2* grid, long nr, double* out, hipStream_t st) {
   return BSE_OK;
 }
 
-int transition_density(const double2* phir, const double2* a, int nv, int nb, long nr,
-                       double2* drho, hipStream_t st) {
-  const long n = (long)((nb + TD_B - 1) / TD_B) * nr;
-  if (n <= 0) return BSE_OK;
-  hipLaunchKernelGGL((k_transition_density<double2, double>), dim3(nblocks(n)), dim3(TPB), 0, st,
-                     phir, a, (nv + 1) / 2, nb, nr, drho);
+// 8 vectors a thread from 2^18 points on (8 vectors of 200 bands at 64^3, FP64:
+// 0.67 ms, 1.01 with 2), below that 2: 5 vectors of 107 bands at 32^3 take
+// 26 us, with 8 a thread and one orbital pair at a time 96; 8 of 180 at 48^3 in
+// FP32 0.20 and 0.39 ms; 5 of 16 at 24^3 3.5 and 14 us
+template <typename V2, typename R>
+static int launch_transition_density(const V2* phir, const V2* a, int nv, int nb, long nr, V2* drho,
+                                     hipStream_t st) {
+  if (nb <= 0 || nr <= 0) return BSE_OK;
+  const int tb = nb == 1 ? 1 : nb == 2 || nr < (1L << 18) ? 2 : 8;
+  const long gx = (nr + 255) / 256, gy = ((long)nb + tb - 1) / tb;
+  if (gx > 0x7fffffffL || gy > 65535) return fail(BSE_EINVAL, "transition density: block too large");
+  const dim3 grid((unsigned)gx, (unsigned)gy);
+  const int nvh = (nv + 1) / 2;
+  if (tb == 1)
+    hipLaunchKernelGGL((k_transition_density<V2, R, 1>), grid, dim3(256), 0, st, phir, a, nvh, nb,
+                       nr, drho);
+  else if (tb == 2)
+    hipLaunchKernelGGL((k_transition_density<V2, R, 2>), grid, dim3(256), 0, st, phir, a, nvh, nb,
+                       nr, drho);
+  else
+    hipLaunchKernelGGL((k_transition_density<V2, R, 8>), grid, dim3(256), 0, st, phir, a, nvh, nb,
+                       nr, drho);
   CHECK_LAUNCH();
   return BSE_OK;
 }
 
+int transition_density(const double2* phir, const double2* a, int nv, int nb, long nr,
+                       double2* drho, hipStream_t st) {
+  return launch_transition_density<double2, double>(phir, a, nv, nb, nr, drho, st);
+}
+
 int transition_density(const float2* phir, const float2* a, int nv, int nb, long nr, float2* drho,
                        hipStream_t st) {
-  const long n = (long)((nb + TD_B - 1) / TD_B) * nr;
-  if (n <= 0) return BSE_OK;
-  hipLaunchKernelGGL((k_transition_density<float2, float>), dim3(nblocks(n)), dim3(TPB), 0, st,
-                     phir, a, (nv + 1) / 2, nb, nr, drho);
-  CHECK_LAUNCH();
-  return BSE_OK;
+  return launch_transition_density<float2, float>(phir, a, nv, nb, nr, drho, st);
 }
 
 __global__ void k_to_f32(const double* __restrict__ x, float* __restrict__ y, long n) {

@@ -1,6 +1,7 @@
 """The matrix products at the edges of their tile and split rules: outputs of
 up to 16 rows, of one 32 x 32 tile and a remainder, inner lengths from a
-single K step to more than 16 splits.  Apply (projector, PDEP products) and
+single K step to more than 16 splits; and the transition density's groups of
+1, 2 and 8 vectors a thread (the last from 2^18 grid points on).  Apply (projector, PDEP products) and
 the U vector (its S matrix) against the FP64 oracle.
 
 Tolerances as in the other parity tests: FP64 1e-11 of the largest entry,
@@ -20,7 +21,8 @@ pytestmark = pytest.mark.gpu
 from paper_2607_20728_amd import bsex  # noqa: E402
 
 # grid edge, n_val, n_pdep, trial vectors: n_pw is about 0.11 edge^3
-SIZES = [(8, 3, 5, 1), (12, 16, 33, 1), (16, 17, 64, 2), (24, 33, 130, 1), (32, 16, 17, 3)]
+SIZES = [(8, 3, 5, 1), (12, 16, 33, 1), (16, 17, 64, 2), (24, 33, 130, 1), (32, 16, 17, 3),
+         (64, 3, 5, 3)]
 
 
 @pytest.mark.parametrize("n,nv,npd,nb", SIZES)
