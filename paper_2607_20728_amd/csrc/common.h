@@ -187,7 +187,8 @@ int pairs_axis(const FftPlan& p, const double2* orb, int nv, const int2* IJ, lon
                double2* data, hipStream_t st);
 int pairs_axis(const FftPlan& p, const float2* orb, int nv, const int2* IJ, long nblk,
                float2* data, hipStream_t st);
-int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc,
+// M[0..nm) times each of the nx fields from component xc of x2 on (two per grid)
+int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc, int nx,
                double2* data, hipStream_t st);
 int planes_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,
                       double2* compact, hipStream_t st);

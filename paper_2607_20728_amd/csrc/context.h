@@ -47,11 +47,13 @@ struct bse_ctx {
   double* fxc = nullptr;      // [nr] f_xc at the ground-state density
   double* rho_ks = nullptr;   // [nr] ground-state density 2 sum phi^2
   double alpha = 0.0;         // exact-exchange fraction alpha_EXX of H_KS
-  double2* xpair = nullptr;   // [nvh][nr] pair grids of the exchange terms
+  double2* xpair = nullptr;   // [xpair_sets][nvh][nr] pair grids of the exchange terms
+  int xpair_sets = 0;
   // PDEP work of the exchange form of W (coupling beyond the TDA):
   // sphere coefficients [nv][npw], PDEP projections [nv][npdep], result [nv][npw]
+  int wx_sets = 0;            // bands that the next four hold
   double *wx_RS = nullptr, *wx_T = nullptr, *wx_F = nullptr;
-  double2* wx_cmp = nullptr;  // [nvh][npw] sphere entries of the pair transforms
+  double2* wx_cmp = nullptr;  // [wx_sets][nvh][npw] sphere entries of the pair transforms
   double2* xgrid = nullptr;   // [xgrid_sets][nvh][nr] -alpha K_x a of an apply block
   int xgrid_sets = 0;
   double t_gs_ms = 0, t_tau_ms = 0, t_tau_alloc_ms = 0, t_init_ms = 0;  // init stages, wall

@@ -230,9 +230,9 @@ int pairs_axis(const FftPlan& p, const float2* orb, int nv, const int2* IJ, long
                hipStream_t st) {
   return f32::pairs_axis(p, orb, nv, IJ, nblk, data, st);
 }
-int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc,
+int times_axis(const FftPlan& p, const double2* M, long nm, const double2* x2, int xc, int nx,
                double2* data, hipStream_t st) {
-  return f64::times_axis(p, M, nm, x2, xc, data, st);
+  return f64::times_axis(p, M, nm, x2, xc, nx, data, st);
 }
 int planes_to_compact(const FftPlan& p, const SpherePlan& sp, double2* grid, long batch,
                       double2* compact, hipStream_t st) {

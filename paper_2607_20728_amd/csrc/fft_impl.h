@@ -965,8 +965,8 @@ __global__ __launch_bounds__(kThreads) void k_fft_axis_field(cplx* __restrict__ 
 //    holds phi_{8I+2m} phi_{8J+j} + i phi_{8I+2m+1} phi_{8J+j} (the tile
 //    layout of the pair-density kernel); orbital v is the real (v even) or
 //    imaginary (v odd) part of packed grid v / 2 of orb, zero for v >= nv;
-//  * IJ NULL (exchange-like terms): grid q < ngrid holds orb[q] times the
-//    real field x (component xc of the packed grid x2).
+//  * IJ NULL (exchange-like terms): grid q < ngrid holds orb[q % nv] times
+//    the real field x_c, c = xc + q / nv (two fields per packed grid of x2).
 // The 32 grids of one group of 32 and one line tile run on one XCD
 // (xcd_item), where they share their common factors' lines in L2.
 template <int N>
@@ -994,7 +994,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_axis_pairs(cplx* __restrict__ 
   const int i0 = tile * L;
   const int nl = min(L, np2 - i0);
   const cplx *oa, *ow;
-  bool a_ok = true, a1_ok = true, w_ok = true, w_im = xc != 0;
+  bool a_ok = true, a1_ok = true, w_ok = true, w_im;
   if (IJ) {
     const int2 b = IJ[blk];
     const int va = 8 * b.x + 2 * (sub & 3), vw = 8 * b.y + (sub >> 2);
@@ -1006,8 +1006,10 @@ __global__ __launch_bounds__(kThreads) void k_fft_axis_pairs(cplx* __restrict__ 
     oa = orb + (long)(va >> 1) * nr + i0;
     ow = orb + (long)(vw >> 1) * nr + i0;
   } else {
-    oa = orb + q * nr + i0;
-    ow = x2 + i0;
+    const long c = xc + q / nv;
+    oa = orb + q % nv * nr + i0;
+    ow = x2 + (c >> 1) * nr + i0;
+    w_im = (c & 1) != 0;
   }
   cplx* out = data + q * nr + i0;
   auto ld = [=](int k, int l) {
@@ -1624,10 +1626,10 @@ int pairs_axis(const FftPlan& p, const cplx* orb, int nv, const int2* IJ, long n
   return axis_pairs(p, orb, nv, IJ, nullptr, 0, nblk * 32, data, st);
 }
 
-int times_axis(const FftPlan& p, const cplx* M, long nm, const cplx* x2, int xc, cplx* data,
+int times_axis(const FftPlan& p, const cplx* M, long nm, const cplx* x2, int xc, int nx, cplx* data,
                hipStream_t st) {
-  if (nm <= 0) return BSE_OK;
-  return axis_pairs(p, M, 0, nullptr, x2, xc, nm, data, st);
+  if (nm <= 0 || nx <= 0) return BSE_OK;
+  return axis_pairs(p, M, (int)nm, nullptr, x2, xc, nm * nx, data, st);
 }
 
 int fft3d_fwd_pairs(const FftPlan& p, const SpherePlan& sp, const cplx* orb, int nv,
@@ -1642,7 +1644,7 @@ int fft3d_fwd_times(const FftPlan& p, const SpherePlan& sp, const cplx* M, long 
                     const cplx* x2, int xc, cplx* data, const real* f, real s, cplx* compact,
                     hipStream_t st) {
   if (nm <= 0) return BSE_OK;
-  BSE_TRY(axis_pairs(p, M, 0, nullptr, x2, xc, nm, data, st));
+  BSE_TRY(axis_pairs(p, M, (int)nm, nullptr, x2, xc, nm, data, st));
   return plane_fwd_w(p, sp, data, nm, f, s, compact, st);
 }
 

@@ -133,11 +133,12 @@ int xc_fields(const double2* rho_occ, long nr, double occ, double floor_, double
 // exchange-like terms sum_w L_w (v_c * (M_w x)): pair grids (M_2q x, M_2q+1 x)
 // for the real grid function x = component xc of x2 (M holds nv functions
 // packed two per complex grid; an odd nv leaves the last .y of M zero), and
-// o2.{x|y}(r) += scale sum_w L_w(r) P_w(r)
+// o2.{x|y}(r) += scale sum_w L_w(r) P_w(r); contract_pairs for nx outputs, two
+// per packed grid from component oc of o2 on, the P of each after the last
 int pair_times(const double2* M, int nv, const double2* x2, int xc, long nr, double2* out,
                hipStream_t st);
 int contract_pairs(const double2* L, const double2* P, int nv, long nr, double2* o2, int oc,
-                   double scale, hipStream_t st);
+                   int nx, double scale, hipStream_t st);
 // w <- scale (w + f_xc t) on ngrid complex grids (f_Hxc * t once w = v_c * t)
 int hxc_field(double2* w, const double2* t, const double* fxc, long ngrid, long nr, double scale,
               hipStream_t st);

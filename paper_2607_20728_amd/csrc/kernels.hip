@@ -815,22 +815,23 @@ __global__ void k_pair_times(const double2* __restrict__ M, int nvh, const doubl
 }
 
 // out (component oc of the packed grid o2) += scale sum_w L_w(r) P_w(r)
-__global__ void k_contract_pairs(const double2* __restrict__ L, const double2* __restrict__ P,
-                                 int nvh, long nr, double2* __restrict__ o2, int oc,
-                                 double scale) {
-  for (long r = gtid(); r < nr; r += gstride()) {
-    double s = 0.0;
-    for (int q = 0; q < nvh; ++q) {
-      const double2 l = L[(long)q * nr + r], p = P[(long)q * nr + r];
-      s += l.x * p.x + l.y * p.y;
-    }
-    double2 o = o2[r];
-    if (oc)
-      o.y += scale * s;
-    else
-      o.x += scale * s;
-    o2[r] = o;
+// (a thread writes its component only: the other one is the next output's)
+__global__ __launch_bounds__(256) void k_contract_pairs(const double2* __restrict__ L,
+                                                        const double2* __restrict__ P, int nvh,
+                                                        long nr, double* __restrict__ o2, int oc,
+                                                        double scale) {
+  const long r = (long)blockIdx.x * 256 + threadIdx.x;
+  if (r >= nr) return;
+  const int c = oc + blockIdx.y;
+  const double2* p = P + (long)blockIdx.y * nvh * nr + r;
+  const double2* l = L + r;
+  double s = 0.0;
+#pragma unroll 4
+  for (int q = 0; q < nvh; ++q) {
+    const double2 a = l[(long)q * nr], b = p[(long)q * nr];
+    s += a.x * b.x + a.y * b.y;
   }
+  o2[2 * ((long)(c >> 1) * nr + r) + (c & 1)] += scale * s;
 }
 
 // occupied density sum_v phi_v(r)^2 (two orbitals per complex grid)
@@ -1178,9 +1179,12 @@ int pair_times(const double2* M, int nv, const double2* x2, int xc, long nr, dou
 }
 
 int contract_pairs(const double2* L, const double2* P, int nv, long nr, double2* o2, int oc,
-                   double scale, hipStream_t st) {
-  hipLaunchKernelGGL(k_contract_pairs, dim3(nblocks(nr)), dim3(TPB), 0, st, L, P, (nv + 1) / 2,
-                     nr, o2, oc, scale);
+                   int nx, double scale, hipStream_t st) {
+  const long gx = (nr + 255) / 256;
+  if (nr <= 0 || nx <= 0) return BSE_OK;
+  if (gx > 0x7fffffffL || nx > 65535) return fail(BSE_EINVAL, "contract pairs: too many outputs");
+  hipLaunchKernelGGL(k_contract_pairs, dim3((unsigned)gx, (unsigned)nx), dim3(256), 0, st, L, P,
+                     (nv + 1) / 2, nr, reinterpret_cast<double*>(o2), oc, scale);
   CHECK_LAUNCH();
   return BSE_OK;
 }

@@ -611,6 +611,17 @@ int ensure_ygrid(bse_ctx* c) {
   return ctx_alloc_t(c, &c->ygrid, (size_t)c->nbc * c->nvh * c->basis.nr);
 }
 
+// pair grids of `sets` bands in the exchange terms
+static int ensure_xpair(bse_ctx* c, int sets) {
+  if (c->xpair_sets >= sets) return BSE_OK;
+  ctx_release(c, c->xpair);
+  c->xpair = nullptr;
+  c->xpair_sets = 0;
+  BSE_TRY(ctx_alloc_t(c, &c->xpair, (size_t)sets * c->nvh * c->basis.nr));
+  c->xpair_sets = sets;
+  return BSE_OK;
+}
+
 // out_v += scale sum_w L_w (v_c * (M_w x_v)) for the nx real grid functions
 // x_v (packed two per complex grid, like out); L and M hold the nv occupied-
 // sized functions of the exact-exchange terms (SM Sec. I).  One Poisson solve
@@ -618,12 +629,12 @@ int ensure_ygrid(bse_ctx* c) {
 int exchange_like(bse_ctx* c, const double2* L, const double2* M, const double2* x, int nx,
                   double2* out, double scale) {
   const long nr = c->basis.nr;
-  if (!c->xpair) BSE_TRY(ctx_alloc_t(c, &c->xpair, (size_t)c->nvh * nr));
+  BSE_TRY(ensure_xpair(c, 1));
   double2* P = c->xpair;
   for (int v = 0; v < nx; ++v) {
     BSE_TRY(pair_times(M, c->nv, x + (long)(v >> 1) * nr, v & 1, nr, P, c->st));
     BSE_TRY(poisson(c, P, c->nvh, 1.0 / (double)nr));
-    BSE_TRY(contract_pairs(L, P, c->nv, nr, out + (long)(v >> 1) * nr, v & 1, scale, c->st));
+    BSE_TRY(contract_pairs(L, P, c->nv, nr, out + (long)(v >> 1) * nr, v & 1, 1, scale, c->st));
   }
   return BSE_OK;
 }
@@ -651,6 +662,38 @@ static int finish_apply(bse_ctx* c, int nb, const double* A, int with_v, double*
   return proj_c(c, c->Zs, Y, nb);
 }
 
+// bands per pass of w_exchange_like: until the plane kernels have 8192
+// workgroups or the pair grids fill half of the last-level cache (128 MB).
+// One band's 24 grids of 32^3 left most of the device idle through nine
+// launches: two vectors of 48 bands took 6.65 ms one band at a time, 2.33 with 10.
+static int wx_sets(const bse_ctx* c, int nx) {
+  const long grids = c->nvh, bytes = 16L * c->basis.nr * grids;
+  long k = 1;
+  while (k < nx && k * grids * c->fft.N[0] < 8192 && (k + 1) * bytes <= (128L << 20)) ++k;
+  return (int)k;
+}
+
+// scratch of `sets` bands: pair grids and, for the PDEP part, their sphere
+// rows (two per grid), coefficients and compact entries
+static int ensure_wx(bse_ctx* c, int sets, bool pdep) {
+  BSE_TRY(ensure_xpair(c, sets));
+  if (!pdep || c->wx_sets >= sets) return BSE_OK;
+  const size_t rows = 2 * (size_t)sets * c->nvh, npw = c->basis.npw;
+  ctx_release(c, c->wx_RS);
+  ctx_release(c, c->wx_T);
+  ctx_release(c, c->wx_F);
+  ctx_release(c, c->wx_cmp);
+  c->wx_RS = c->wx_T = c->wx_F = nullptr;
+  c->wx_cmp = nullptr;
+  c->wx_sets = 0;
+  BSE_TRY(ctx_alloc_t(c, &c->wx_RS, rows * npw));
+  BSE_TRY(ctx_alloc_t(c, &c->wx_T, rows * c->npdep));
+  BSE_TRY(ctx_alloc_t(c, &c->wx_F, rows * npw));
+  BSE_TRY(ctx_alloc_t(c, &c->wx_cmp, rows / 2 * npw));
+  c->wx_sets = sets;
+  return BSE_OK;
+}
+
 // out_v += scale sum_w L_w [W (M_w x_v)] for the nx real grid functions x_v
 // (packed like out): the exchange form of W, the bare Coulomb part and, by
 // the kernel mask, the PDEP part of Eq. 3 (two GEMMs on the sphere
@@ -661,28 +704,42 @@ static int w_exchange_like(bse_ctx* c, const double2* L, const double2* M, const
   const int nv = c->nv;
   const bool bare = (c->kmask & BSE_K_1D_BARE) != 0;
   const bool pdep = (c->kmask & BSE_K_1D_PDEP) && c->npdep > 0;
-  if (!c->xpair) BSE_TRY(ctx_alloc_t(c, &c->xpair, (size_t)c->nvh * nr));
-  if (pdep && !c->wx_RS) {
-    BSE_TRY(ctx_alloc_t(c, &c->wx_RS, (size_t)nv * npw));
-    BSE_TRY(ctx_alloc_t(c, &c->wx_T, (size_t)nv * c->npdep));
-    BSE_TRY(ctx_alloc_t(c, &c->wx_F, (size_t)nv * npw));
-    BSE_TRY(ctx_alloc_t(c, &c->wx_cmp, (size_t)c->nvh * npw));
-  }
-  double2* P = c->xpair;
   SphereMap m = c->map;
   const bool planes = w_planes_on(c, false);
   const bool fused = planes || w_fused_on(), pairs = w_pairs_on(c, false);
-  for (int v = 0; v < nx; ++v) {
+  int nk = planes && pairs ? wx_sets(c, nx) : 1;
+  if (ensure_wx(c, nk, pdep) != BSE_OK) {
+    nk = 1;  // as little scratch as there can be
+    BSE_TRY(ensure_wx(c, nk, pdep));
+  }
+  double2* P = c->xpair;
+  for (int v = 0; v < nx; v += nk) {
     const double2* xv = x + (long)(v >> 1) * nr;
+    // the orbital rows of k bands' grids: an odd nv's last grid counts as two
+    const int k = std::min(nk, nx - v), ng = k * c->nvh, ne = 2 * ng;
     if (planes) {
       if (pairs) {
-        BSE_TRY(times_axis(c->fft, M, c->nvh, xv, v & 1, P, c->st));
+        BSE_TRY(times_axis(c->fft, M, c->nvh, xv, v & 1, k, P, c->st));
       } else {
         BSE_TRY(pair_times(M, nv, xv, v & 1, nr, P, c->st));
         BSE_TRY(fft3d_axis(c->fft, P, c->nvh, -1, c->st));
       }
-      if (pdep) BSE_TRY(planes_to_compact(c->fft, c->sp, P, c->nvh, c->wx_cmp, c->st));
-    } else if (pairs) {
+      if (pdep) {
+        BSE_TRY(planes_to_compact(c->fft, c->sp, P, ng, c->wx_cmp, c->st));
+        BSE_TRY(gather_sets(c->cmap, c->wx_cmp, 2 * c->nvh, k, 1.0 / (double)nr, nullptr, nullptr,
+                            nullptr, 0.0, 0.0, c->wx_RS, c->st));
+        BSE_TRY(gemm(c, 0, 0, ne, c->npdep, npw, 1.0, c->wx_RS, npw, c->Pt, c->npdep, 0.0,
+                     c->wx_T, c->npdep));
+        BSE_TRY(dgemm(0, 1, ne, npw, c->npdep, 1.0, c->wx_T, c->npdep, c->Ptc, c->npdep, 0.0,
+                      c->wx_F, npw, c->st));
+      }
+      BSE_TRY(fft3d_w_planes(c->fft, c->sp, P, ng, bare ? c->vc : nullptr, 1.0 / (double)nr,
+                             pdep ? c->wx_F : nullptr, nullptr, ne, c->basis.omega, c->st));
+      BSE_TRY(fft3d_axis(c->fft, P, ng, +1, c->st));
+      BSE_TRY(contract_pairs(L, P, nv, nr, out + (long)(v >> 1) * nr, v & 1, k, scale, c->st));
+      continue;
+    }
+    if (pairs) {
       BSE_TRY(fft3d_fwd_times(c->fft, c->sp, M, c->nvh, xv, v & 1, P, bare ? c->vc : nullptr,
                               1.0 / (double)nr, pdep ? c->wx_cmp : nullptr, c->st));
     } else {
@@ -705,15 +762,9 @@ static int w_exchange_like(bse_ctx* c, const double2* L, const double2* M, const
       BSE_TRY(mul_real_field(P, c->nvh, nr, c->vc, 1.0 / (double)nr, c->st));
     else if (!fused)
       BSE_TRY(zero_fill(reinterpret_cast<double*>(P), 2L * c->nvh * nr, c->st));
-    if (planes) {
-      BSE_TRY(fft3d_w_planes(c->fft, c->sp, P, c->nvh, bare ? c->vc : nullptr, 1.0 / (double)nr,
-                             pdep ? c->wx_F : nullptr, nullptr, nv, c->basis.omega, c->st));
-      BSE_TRY(fft3d_axis(c->fft, P, c->nvh, +1, c->st));
-    } else {
-      if (pdep) BSE_TRY(scatter_sets(m, c->wx_F, nv, 1, P, 1, c->st));
-      BSE_TRY(fft3d(c->fft, P, c->nvh, +1, c->st));
-    }
-    BSE_TRY(contract_pairs(L, P, nv, nr, out + (long)(v >> 1) * nr, v & 1, scale, c->st));
+    if (pdep) BSE_TRY(scatter_sets(m, c->wx_F, nv, 1, P, 1, c->st));
+    BSE_TRY(fft3d(c->fft, P, c->nvh, +1, c->st));
+    BSE_TRY(contract_pairs(L, P, nv, nr, out + (long)(v >> 1) * nr, v & 1, 1, scale, c->st));
   }
   return BSE_OK;
 }
