@@ -137,17 +137,29 @@ struct Rot {
 // begin at any column can be read and written.
 constexpr int kL = 16;
 typedef double v4 __attribute__((vector_size(32), aligned(8)));
+// Each kernel is compiled for the baseline and for AVX2 (without FMA) and
+// picks by the CPU.
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
-#define LANES __attribute__((target_clones("avx2", "default")))
+bool wide() {
+  static const bool w = __builtin_cpu_supports("avx2");
+  return w;
+}
+#define LANES_WIDE __attribute__((target("avx2")))
 #else
-#define LANES
+bool wide() { return false; }
+#define LANES_WIDE
 #endif
+#define LANES __attribute__((always_inline)) inline
+#define LANES_PICK(name, params, args)         \
+  LANES_WIDE void name##_wide params { name##_body args; } \
+  void name##_base params { name##_body args; }            \
+  inline void name params { wide() ? name##_wide args : name##_base args; }
 
 int padded(int n) { return (n + kL - 1) / kL * kL + kL; }
 
 // p[i] = b (sum_j B[j][i] v[j]), even and odd j summed apart; blocks [b0, b1)
 // of i < m
-LANES void symv_block(int b0, int b1, int m, const double* B, int ld, const double* v, double b,
+LANES void symv_block_body(int b0, int b1, int m, const double* B, int ld, const double* v, double b,
                       double* p) {
 #pragma clang fp contract(off)
   for (int q = b0; q < b1; ++q) {
@@ -164,10 +176,13 @@ LANES void symv_block(int b0, int b1, int m, const double* B, int ld, const doub
     for (int l = 0; l < 4; ++l) *(v4*)(p + q * kL + 4 * l) = b * (s[l] + t[l]);
   }
 }
+LANES_PICK(symv_block,
+           (int b0, int b1, int m, const double* B, int ld, const double* v, double b, double* p),
+           (b0, b1, m, B, ld, v, b, p))
 
 // columns [b0, b1) (blocks) of B -= v w^T + w v^T, m rows.  Split like
 // symv_block, so a worker reads what it wrote.
-LANES void rank2_block(int b0, int b1, int m, double* B, int ld, const double* v, const double* w) {
+LANES void rank2_block_body(int b0, int b1, int m, double* B, int ld, const double* v, const double* w) {
 #pragma clang fp contract(off)
   const int c0 = b0 * kL, c1 = b1 * kL < m ? b1 * kL : m;
   for (int i = 0; i < m; ++i) {
@@ -178,9 +193,12 @@ LANES void rank2_block(int b0, int b1, int m, double* B, int ld, const double* v
     for (; j < c1; ++j) x[j] -= vi * w[j] + wi * v[j];
   }
 }
+LANES_PICK(rank2_block,
+           (int b0, int b1, int m, double* B, int ld, const double* v, const double* w),
+           (b0, b1, m, B, ld, v, w))
 
 // columns [b0, b1) (blocks) of X <- (1 - b v v^T) X, m rows
-LANES void reflect_block(int b0, int b1, int m, double* X, int ld, const double* v, double b) {
+LANES void reflect_block_body(int b0, int b1, int m, double* X, int ld, const double* v, double b) {
 #pragma clang fp contract(off)
   for (int q = b0; q < b1; ++q) {
     double* x = X + q * kL;
@@ -192,10 +210,13 @@ LANES void reflect_block(int b0, int b1, int m, double* X, int ld, const double*
       for (int l = 0; l < 4; ++l) *(v4*)(x + (size_t)i * ld + 4 * l) -= s[l] * v[i];
   }
 }
+LANES_PICK(reflect_block,
+           (int b0, int b1, int m, double* X, int ld, const double* v, double b),
+           (b0, b1, m, X, ld, v, b))
 
 // the rotations on the rows of a dense block of kL columns; the row that two
 // successive rotations share stays in registers
-LANES void rotate_block(const Rot* rots, size_t nrot, double* band) {
+LANES void rotate_block_body(const Rot* rots, size_t nrot, double* band) {
 #pragma clang fp contract(off)
   v4 c[4];
   int held = -1;
@@ -217,9 +238,10 @@ LANES void rotate_block(const Rot* rots, size_t nrot, double* band) {
   if (held >= 0)
     for (int l = 0; l < 4; ++l) *(v4*)(band + (size_t)held * kL + 4 * l) = c[l];
 }
+LANES_PICK(rotate_block, (const Rot* rots, size_t nrot, double* band), (rots, nrot, band))
 
 // t[i] = a[i] - sum_{k < m} f[k] X[k][i], k ascending, one block of i
-LANES void fold_block(int m, const double* f, const double* X, int ld, double* t) {
+LANES void fold_block_body(int m, const double* f, const double* X, int ld, double* t) {
 #pragma clang fp contract(off)
   v4 s[4];
   for (int l = 0; l < 4; ++l) s[l] = *(const v4*)(t + 4 * l);
@@ -229,6 +251,9 @@ LANES void fold_block(int m, const double* f, const double* X, int ld, double* t
   }
   for (int l = 0; l < 4; ++l) *(v4*)(t + 4 * l) = s[l];
 }
+LANES_PICK(fold_block,
+           (int m, const double* f, const double* X, int ld, double* t),
+           (m, f, X, ld, t))
 
 // A <- Q^T A Q tridiagonal (A symmetric, rows ld apart).  Reflector k,
 // I - beta_k v_k v_k^T acting on indices k+1..n-1, is kept in row k of V
