@@ -521,10 +521,11 @@ __device__ __forceinline__ void fn_passes(LD ld, ST st, cplx* S0, cplx* S1, int 
 // HBM (one read and one write of the grids) where two or more fit.  With the
 // forward and inverse transforms as kernels of their own (through scratch
 // lines in LDS, the grids written and read between them) and a scatter, FP64
-// 64^3, 10,400 grids: 31.5 + 5.4 + 25.2 ms, now 11.8 for the sphere entries
-// and 23.9 here (3.6 TB/s); 72^3, 8,544 grids: 35.9 + 3.4 + 30.0, now 10.2 +
-// 39.2 (2.6 TB/s, one workgroup per CU); FP32 48 x 120: 13.9 + 5.7 + 12.2,
-// now 11.8 + 16.3.
+// 64^3, 10,400 grids: 31.5 + 5.4 + 25.2 ms, now 6.9 for the sphere entries
+// and 23.8 here (3.6 TB/s); 72^3, 8,544 grids: 35.9 + 3.4 + 30.0, now 10.8 +
+// 38.9 (2.6 TB/s, one workgroup per CU; as one workgroup per CU that reads the
+// next plane into registers meanwhile 50.8, for the registers spilled); FP32
+// 48 x 120: 13.9 + 5.7 + 12.2, now 5.8 + 15.9.
 // ---------------------------------------------------------------------------
 template <int N2, int N3>
 constexpr int wp_rs() {
@@ -662,11 +663,13 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N
 #pragma unroll 4
     for (int e = threadIdx.x; e < NP2; e += NT) P[e / N3 * RS + e % N3] = gp[e];
     __syncthreads();
-    lines_inplace<N3, -1, N2, NT, 0, 1>(NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+    lines_inplace<N3, -1, N2, NT, 0, 1>(
+        NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
     __syncthreads();
     const real* f = wa.f + (long)i1 * NP2;
     const real s = wa.s;
-    lines_inplace<N2, -1, N3, NT, 0, 1>(NlAll<N3>(), col, [=](int k, int l) { return f[k * N3 + l]; },
+    lines_inplace<N2, -1, N3, NT, 0, 1>(
+        NlAll<N3>(), col, [=](int k, int l) { return f[k * N3 + l]; },
         [=](int k, int l, cplx v, real m) {
           m *= s;
           v.x *= m;
@@ -701,9 +704,11 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N
     }
     __syncthreads();
   }
-  lines_inplace<N3, 1, N2, NT, 0, 1>(NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
+  lines_inplace<N3, 1, N2, NT, 0, 1>(
+      NlAll<N2>(), row, none, [=](int k, int l, cplx v, int) { *row(k, l) = v; }, tw3);
   __syncthreads();
-  lines_inplace<N2, 1, N3, NT, 0, 1>(NlAll<N3>(), col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
+  lines_inplace<N2, 1, N3, NT, 0, 1>(
+      NlAll<N3>(), col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
 }
 
 // ---------------------------------------------------------------------------

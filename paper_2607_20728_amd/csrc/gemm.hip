@@ -1,8 +1,8 @@
 // FP64 and FP32 GEMMs on the CDNA matrix cores (v_mfma_f64_16x16x4f64,
 // v_mfma_f32_16x16x4f32).
 //
-// Workgroup tile BM x 64, K step 16 staged through LDS (the next step's
-// tiles are held in registers meanwhile), four waves.  BM = 64:
+// Workgroup tile BM x 64, K steps of 16 (32 in FP32) through two LDS buffers
+// (the next step's tiles are held in registers meanwhile), four waves.  BM = 64:
 // the waves own 32 x 32 quarters as 2 x 2 MFMA tiles.  BM = 16, for outputs
 // of at most 16 rows (the solvers' products of a few vectors with a whole
 // subspace): the waves own the four 16 x 16 tiles side by side, so no matrix
@@ -404,7 +404,8 @@ void launch_form(const Tiling& t, dim3 grid, hipStream_t st, Args... args) {
 
 // few: below this many workgroups the latency forms serve.  FP64 fills a
 // CU's matrix units from one workgroup, FP32 (half the time per instruction)
-// needs more in flight.
+// needs more in flight: 3,400 x 256 x 60,000 in 212 full tiles takes 2.00 ms,
+// in 848 small ones 1.73.
 template <typename T>
 int launch(int ta, int tb, long M, long N, long K, T alpha, const T* A, long lda, const T* B,
            long ldb, T beta, const T* Cin, T* C, long ldc, long kc, long cstride, long s,
@@ -412,7 +413,8 @@ int launch(int ta, int tb, long M, long N, long K, T alpha, const T* A, long lda
   const Tiling t = tiling(M, N, K, s, sizeof(T) == 8 ? 256 : 512);
   const int by_row = t.nt < t.mt && xcd_group_on() ? 1 : 0;
   const long nwg = (by_row ? round8(t.mt) : t.mt) * t.nt;
-  if (nwg > 0x7fffffffL || M > 0xffffffffL || N > 0xffffffffL || s > 65535) return fail(BSE_EINVAL, "gemm: output too large for the grid");
+  if (nwg > 0x7fffffffL || M > 0xffffffffL || N > 0xffffffffL || s > 65535)
+    return fail(BSE_EINVAL, "gemm: output too large for the grid");
   const dim3 grid((unsigned)nwg, 1, (unsigned)s);
   const int ntn = (int)t.nt;
 #define GO(TA_, TB_)                                                                             \

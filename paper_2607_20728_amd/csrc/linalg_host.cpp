@@ -159,8 +159,8 @@ int padded(int n) { return (n + kL - 1) / kL * kL + kL; }
 
 // p[i] = b (sum_j B[j][i] v[j]), even and odd j summed apart; blocks [b0, b1)
 // of i < m
-LANES void symv_block_body(int b0, int b1, int m, const double* B, int ld, const double* v, double b,
-                      double* p) {
+LANES void symv_block_body(int b0, int b1, int m, const double* B, int ld, const double* v,
+                           double b, double* p) {
 #pragma clang fp contract(off)
   for (int q = b0; q < b1; ++q) {
     const double* x = B + q * kL;
@@ -182,7 +182,8 @@ LANES_PICK(symv_block,
 
 // columns [b0, b1) (blocks) of B -= v w^T + w v^T, m rows.  Split like
 // symv_block, so a worker reads what it wrote.
-LANES void rank2_block_body(int b0, int b1, int m, double* B, int ld, const double* v, const double* w) {
+LANES void rank2_block_body(int b0, int b1, int m, double* B, int ld, const double* v,
+                            const double* w) {
 #pragma clang fp contract(off)
   const int c0 = b0 * kL, c1 = b1 * kL < m ? b1 * kL : m;
   for (int i = 0; i < m; ++i) {
