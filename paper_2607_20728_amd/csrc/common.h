@@ -249,4 +249,6 @@ int host_cholesky(int n, double* A);
 // in-place inverse of a lower-triangular L (row-major, upper part zero);
 // returns nonzero on a zero or non-finite diagonal
 int host_trinv_lower(int n, double* L);
+// parts that have been split over the host worker threads so far
+long host_pool_runs();
 }  // namespace bsex

@@ -10,12 +10,17 @@
 // The O(n^3) parts work on 16 independent values side by side (four vector
 // registers), laid out so that the sums that belong to one value stay in one
 // lane, in the order of the scalar algorithm, and nothing is contracted: the
-// result does not depend on the vector width.  An eigenproblem of 73 took
-// 0.25 ms on 16 threads and takes 0.21 on one (of 200: 2.6 and now 1.8, of
-// 300: 6.2 and 6.4 ms), a Cholesky factor of 200 with its inverse 0.43 and now
-// 0.20 ms.  From about 200 rows on the parts are split over a small pool of
-// host threads; below that the work is shorter than waking them, which on a
-// busy host takes milliseconds.
+// result does not depend on the vector width.  Matrices are held in blocks of
+// 16 columns, each contiguous and always with the same worker.  On 16 threads
+// (EPYC), against the scalar form split by rows: an eigenproblem of 73 0.29 ms
+// and now 0.24 (one thread), of 100 0.53 and 0.50, of 200 3.0 and 1.95, of 300
+// 6.5 and 4.9, of 400 11.7 and 8.9, of 800 51 and 38; a Cholesky factor of 200
+// with its inverse 0.51 and 0.21, of 600 5.4 and 4.1.
+//
+// A part is split over a small pool of host threads from the work on that
+// pays for waking them: the rotations from about 85 rows, the reflectors' product
+// from 131, the inverse from 208, a reduction step from 224 trailing rows, a
+// Cholesky column from about 550 rows.
 #include <sched.h>
 
 #include <algorithm>
@@ -45,12 +50,14 @@ class Workers {
     return *w;
   }
   int size() const { return n_; }
+  long runs() const { return runs_.load(std::memory_order_relaxed); }
   void run(const std::function<void(int, int)>& fn) {
     std::unique_lock<std::mutex> own(run_mx_, std::try_to_lock);
     if (n_ == 1 || !own.owns_lock()) {
       for (int t = 0; t < n_; ++t) fn(t, n_);
       return;
     }
+    runs_.fetch_add(1, std::memory_order_relaxed);
     job_ = &fn;
     left_.store(n_ - 1, std::memory_order_relaxed);
     {
@@ -104,6 +111,7 @@ class Workers {
   std::condition_variable cv_;
   std::atomic<unsigned> gen_{0};
   std::atomic<int> left_{0};
+  std::atomic<long> runs_{0};
   const std::function<void(int, int)>* job_ = nullptr;
 };
 
@@ -122,10 +130,27 @@ void split_range(int m, double flops, double least, F&& fn) {
   });
 }
 
-// least work worth handing out: within a sequence of parts, whose workers are
-// awake (15 us on one thread; from 7e4 on, 200 rows took 2.2 ms for 1.8 and 300
-// rows 9.3 for 6.4), and for a part by itself
-constexpr double kSplitStep = 1.5e5, kSplitOnce = 8.0e6;
+// fn(q) for the blocks [q0, q1), block q always on the same worker
+template <class F>
+void deal_blocks(int q0, int q1, double flops, double least, F&& fn) {
+  Workers& w = Workers::get();
+  if (w.size() == 1 || flops < least) {
+    for (int q = q0; q < q1; ++q) fn(q);
+    return;
+  }
+  w.run([&](int t, int nt) {
+    for (int q = q0 + (t - q0 % nt + nt) % nt; q < q1; q += nt) fn(q);
+  });
+}
+
+// Least work worth handing out: a step of the reduction and a column of the
+// Cholesky factor (with workers that are awake from the step before), and a
+// part by itself.  Eigenproblems of 100 / 160 / 240 take 0.54 / 1.31 / 2.95 ms with
+// 3e5 and 8e6, 0.50 / 1.20 / 2.88 with 3e5 and 3e6, 0.46 / 1.20 / 2.93 with 3e5 and
+// 1e6 (but inverses of 160 and 200 0.07 and 0.11 ms for 0.05 and 0.09), 0.50 / 1.21 /
+// 2.95 with 6e5 and 3e6; a Cholesky factor of 800 takes 4.8 ms from 1.5e5 on
+// and 6.8 from 3e5 on.
+constexpr double kSplitReduce = 3.0e5, kSplitColumn = 1.5e5, kSplitOnce = 3.0e6;
 
 struct Rot {
   int k;
@@ -155,65 +180,58 @@ bool wide() { return false; }
   void name##_base params { name##_body args; }            \
   inline void name params { wide() ? name##_wide args : name##_base args; }
 
-int padded(int n) { return (n + kL - 1) / kL * kL + kL; }
+int blocks(int n) { return (n + kL - 1) / kL; }
+int padded(int n) { return blocks(n) * kL + kL; }
 
-// p[i] = b (sum_j B[j][i] v[j]), even and odd j summed apart; blocks [b0, b1)
-// of i < m
-LANES void symv_block_body(int b0, int b1, int m, const double* B, int ld, const double* v,
-                           double b, double* p) {
+// One step of the reduction on a block x of kL columns (rows kL apart), rows
+// [i0, n): the rank-2 update x -= v w^T + w v^T of the step before, where v is
+// given (vj, wj: v and w at the block's columns), and with the rows so updated
+// p = b x^T u, even and odd rows summed apart.
+LANES void reduce_block_body(int i0, int n, double* x, const double* v, const double* w,
+                             const double* vj, const double* wj, const double* u, double b,
+                             double* p) {
 #pragma clang fp contract(off)
-  for (int q = b0; q < b1; ++q) {
-    const double* x = B + q * kL;
-    v4 s[4] = {}, t[4] = {};
-    int j = 0;
-    for (; j + 1 < m; j += 2, x += 2 * (size_t)ld)
-      for (int l = 0; l < 4; ++l) {
-        s[l] += *(const v4*)(x + 4 * l) * v[j];
-        t[l] += *(const v4*)(x + ld + 4 * l) * v[j + 1];
+  v4 s[4] = {}, t[4] = {}, cv[4], cw[4];
+  if (v)
+    for (int l = 0; l < 4; ++l) {
+      cv[l] = *(const v4*)(vj + 4 * l);
+      cw[l] = *(const v4*)(wj + 4 * l);
+    }
+  auto row = [&](int i, v4* sum) __attribute__((always_inline)) {
+    double* r = x + (size_t)i * kL;
+    for (int l = 0; l < 4; ++l) {
+      v4 y = *(const v4*)(r + 4 * l);
+      if (v) {
+        y -= v[i] * cw[l] + w[i] * cv[l];
+        *(v4*)(r + 4 * l) = y;
       }
-    if (j < m)
-      for (int l = 0; l < 4; ++l) s[l] += *(const v4*)(x + 4 * l) * v[j];
-    for (int l = 0; l < 4; ++l) *(v4*)(p + q * kL + 4 * l) = b * (s[l] + t[l]);
+      sum[l] += y * u[i];
+    }
+  };
+  int i = i0;
+  for (; i + 1 < n; i += 2) {
+    row(i, s);
+    row(i + 1, t);
   }
+  if (i < n) row(i, s);
+  for (int l = 0; l < 4; ++l) *(v4*)(p + 4 * l) = b * (s[l] + t[l]);
 }
-LANES_PICK(symv_block,
-           (int b0, int b1, int m, const double* B, int ld, const double* v, double b, double* p),
-           (b0, b1, m, B, ld, v, b, p))
+LANES_PICK(reduce_block,
+           (int i0, int n, double* x, const double* v, const double* w, const double* vj,
+            const double* wj, const double* u, double b, double* p),
+           (i0, n, x, v, w, vj, wj, u, b, p))
 
-// columns [b0, b1) (blocks) of B -= v w^T + w v^T, m rows.  Split like
-// symv_block, so a worker reads what it wrote.
-LANES void rank2_block_body(int b0, int b1, int m, double* B, int ld, const double* v,
-                            const double* w) {
+// rows [i0, n) of a block x of kL columns <- (1 - b v v^T) x
+LANES void reflect_block_body(int i0, int n, double* x, const double* v, double b) {
 #pragma clang fp contract(off)
-  const int c0 = b0 * kL, c1 = b1 * kL < m ? b1 * kL : m;
-  for (int i = 0; i < m; ++i) {
-    double* x = B + (size_t)i * ld;
-    const double vi = v[i], wi = w[i];
-    int j = c0;
-    for (; j + 4 <= c1; j += 4) *(v4*)(x + j) -= vi * *(const v4*)(w + j) + wi * *(const v4*)(v + j);
-    for (; j < c1; ++j) x[j] -= vi * w[j] + wi * v[j];
-  }
+  v4 s[4] = {};
+  for (int i = i0; i < n; ++i)
+    for (int l = 0; l < 4; ++l) s[l] += v[i] * *(const v4*)(x + (size_t)i * kL + 4 * l);
+  for (int l = 0; l < 4; ++l) s[l] *= b;
+  for (int i = i0; i < n; ++i)
+    for (int l = 0; l < 4; ++l) *(v4*)(x + (size_t)i * kL + 4 * l) -= s[l] * v[i];
 }
-LANES_PICK(rank2_block,
-           (int b0, int b1, int m, double* B, int ld, const double* v, const double* w),
-           (b0, b1, m, B, ld, v, w))
-
-// columns [b0, b1) (blocks) of X <- (1 - b v v^T) X, m rows
-LANES void reflect_block_body(int b0, int b1, int m, double* X, int ld, const double* v, double b) {
-#pragma clang fp contract(off)
-  for (int q = b0; q < b1; ++q) {
-    double* x = X + q * kL;
-    v4 s[4] = {};
-    for (int i = 0; i < m; ++i)
-      for (int l = 0; l < 4; ++l) s[l] += v[i] * *(const v4*)(x + (size_t)i * ld + 4 * l);
-    for (int l = 0; l < 4; ++l) s[l] *= b;
-    for (int i = 0; i < m; ++i)
-      for (int l = 0; l < 4; ++l) *(v4*)(x + (size_t)i * ld + 4 * l) -= s[l] * v[i];
-  }
-}
-LANES_PICK(reflect_block,
-           (int b0, int b1, int m, double* X, int ld, const double* v, double b),
-           (b0, b1, m, X, ld, v, b))
+LANES_PICK(reflect_block, (int i0, int n, double* x, const double* v, double b), (i0, n, x, v, b))
 
 // the rotations on the rows of a dense block of kL columns; the row that two
 // successive rotations share stays in registers
@@ -256,78 +274,91 @@ LANES_PICK(fold_block,
            (int m, const double* f, const double* X, int ld, double* t),
            (m, f, X, ld, t))
 
-// A <- Q^T A Q tridiagonal (A symmetric, rows ld apart).  Reflector k,
-// I - beta_k v_k v_k^T acting on indices k+1..n-1, is kept in row k of V
-// (columns k+1..n-1).
+// T = Q^T A Q tridiagonal (d, e), A symmetric in blocks of kL columns, [n][kL]
+// each (overwritten).  Reflector k, I - beta_k v_k v_k^T acting on indices
+// k+1..n-1, is kept in row k of V (rows ld apart, zero up to column k).
+// A block belongs to one worker from the first step to the last and is read
+// and written once a step, the update of a step together with the product of
+// the next: with blocks that began at the step's own column, and two visits, a
+// line changed hands at every row of every step, and an eigenproblem of 400
+// took 17.7 ms.
 void householder_tridiag(int n, int ld, std::vector<double>& A, std::vector<double>& V,
                          std::vector<double>& beta, std::vector<double>& d,
                          std::vector<double>& e) {
-  auto a = [&](int i, int j) -> double& { return A[(size_t)i * ld + j]; };
-  std::vector<double> p(ld), w(ld);
+#pragma clang fp contract(off)
+  const int nq = blocks(n);
+  std::vector<double> p(ld, 0.0), w(ld, 0.0);
+  const double* v0 = nullptr;  // the reflector whose update is still to be made
+  // column k from row k on, with that update
+  auto entry = [&](int i, int k) {
+    const double x = A[((size_t)(k / kL) * n + i) * kL + k % kL];
+    return v0 ? x - (v0[i] * w[k] + w[i] * v0[k]) : x;
+  };
   for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;  // length of the column below the diagonal
-    double* v = &V[(size_t)k * ld + k + 1];
+    const int i0 = k + 1;
+    double* v = &V[(size_t)k * ld];
+    d[k] = entry(k, k);
     double nrm2 = 0.0;
-    for (int i = 0; i < m; ++i) {
-      v[i] = a(k + 1 + i, k);
+    for (int i = i0; i < n; ++i) {
+      v[i] = entry(i, k);
       nrm2 += v[i] * v[i];
     }
-    const double tail = nrm2 - v[0] * v[0];
+    const double tail = nrm2 - v[i0] * v[i0];
     beta[k] = 0.0;
-    if (tail <= 0.0) continue;  // already tridiagonal in this column
-    const double nrm = std::sqrt(nrm2);
-    const double alpha = v[0] > 0 ? -nrm : nrm;
-    v[0] -= alpha;
-    const double bk = 2.0 / (v[0] * v[0] + tail);
-    beta[k] = bk;
-    double* B = &a(k + 1, k + 1);  // the trailing block
-    // p = beta B v
-    split_range((m + kL - 1) / kL, 2.0 * m * m, kSplitStep,
-                [&](int lo, int hi) { symv_block(lo, hi, m, B, ld, v, bk, p.data()); });
+    e[k] = v[i0];
+    const bool skip = tail <= 0.0;  // already tridiagonal in this column
+    if (!skip) {
+      const double nrm = std::sqrt(nrm2);
+      e[k] = v[i0] > 0 ? -nrm : nrm;
+      v[i0] -= e[k];
+      beta[k] = 2.0 / (v[i0] * v[i0] + tail);
+    }
+    if (!skip || v0)
+      deal_blocks(i0 / kL, nq, 6.0 * (n - i0) * (n - i0), kSplitReduce, [&](int q) {
+        reduce_block(i0, n, &A[(size_t)q * n * kL], v0, w.data(), v0 ? v0 + q * kL : nullptr,
+                     &w[q * kL], v, beta[k], &p[q * kL]);
+      });
+    v0 = nullptr;
+    if (skip) continue;
     double pv = 0.0;
-    for (int i = 0; i < m; ++i) pv += p[i] * v[i];
-    const double K = 0.5 * bk * pv;
-    for (int i = 0; i < m; ++i) w[i] = p[i] - K * v[i];
-    split_range((m + kL - 1) / kL, 4.0 * m * m, 2 * kSplitStep,
-                [&](int lo, int hi) { rank2_block(lo, hi, m, B, ld, v, w.data()); });
-    a(k + 1, k) = a(k, k + 1) = alpha;
-    for (int i = 1; i < m; ++i) a(k + 1 + i, k) = a(k, k + 1 + i) = 0.0;
+    for (int i = i0; i < n; ++i) pv += p[i] * v[i];
+    const double K = 0.5 * beta[k] * pv;
+    w[k] = 0.0;
+    for (int i = i0; i < n; ++i) w[i] = p[i] - K * v[i];
+    v0 = v;
   }
-  for (int i = 0; i < n; ++i) d[i] = a(i, i);
-  for (int i = 0; i + 1 < n; ++i) e[i] = a(i + 1, i);
+  if (n > 1) {
+    d[n - 2] = entry(n - 2, n - 2);
+    e[n - 2] = entry(n - 1, n - 2);
+  }
+  d[n - 1] = entry(n - 1, n - 1);
   e[n - 1] = 0.0;
 }
 
-// Q = H_0 H_1 ... H_{n-3}: the reflectors applied to the unit vectors, column
-// j of Q, from the last to the first (H_k leaves e_j alone for k >= j).
-void form_q(int n, int ld, const std::vector<double>& V, const std::vector<double>& beta,
-            std::vector<double>& Q) {
-  for (int j = 0; j < n; ++j) Q[(size_t)j * ld + j] = 1.0;
-  for (int k = n - 3; k >= 0; --k) {
-    if (beta[k] == 0.0) continue;
-    const int m = n - k - 1;
-    double* X = &Q[(size_t)(k + 1) * ld + k + 1];
-    const double* v = &V[(size_t)k * ld + k + 1];
-    split_range((m + kL - 1) / kL, 4.0 * m * m, 2 * kSplitStep,
-                [&](int lo, int hi) { reflect_block(lo, hi, m, X, ld, v, beta[k]); });
-  }
+// Q^T in blocks of kL columns, [n][kL] each (element (r, c) of Q^T at row r of
+// block c / kL), Q = H_0 H_1 ... H_{n-3}: the reflectors applied to the unit
+// vectors, column j of Q, from the last to the first (H_k leaves e_j alone for
+// k >= j), kL columns at a time.
+void form_qt(int n, int ld, const std::vector<double>& V, const std::vector<double>& beta,
+             std::vector<double>& Qt) {
+  const int nq = blocks(n);
+  deal_blocks(0, nq, 4.0 / 3.0 * n * (double)n * n, kSplitOnce, [&](int q) {
+    std::vector<double> x((size_t)nq * kL * kL, 0.0);
+    for (int l = 0; l < kL && q * kL + l < n; ++l) x[(size_t)(q * kL + l) * kL + l] = 1.0;
+    for (int k = std::min(q * kL + kL - 2, n - 3); k >= 0; --k)
+      if (beta[k] != 0.0) reflect_block(k + 1, n, x.data(), &V[(size_t)k * ld], beta[k]);
+    for (int b = 0; b < nq; ++b)
+      for (int l = 0; l < kL && q * kL + l < n; ++l)
+        for (int i = 0; i < kL; ++i)
+          Qt[((size_t)b * n + q * kL + l) * kL + i] = x[(size_t)(b * kL + i) * kL + l];
+  });
 }
 
-// apply recorded plane rotations to the rows of Qt (rows ld apart), a dense
-// copy of one block of columns at a time
-void apply_rotations(int n, const std::vector<Rot>& rots, double* Qt, int ld) {
+// apply recorded plane rotations to the rows of Qt, a block of columns at a time
+void apply_rotations(int n, const std::vector<Rot>& rots, std::vector<double>& Qt) {
   if (rots.empty()) return;
-  split_range((n + kL - 1) / kL, 6.0 * (double)rots.size() * n, kSplitOnce, [&](int lo, int hi) {
-    std::vector<double> band((size_t)n * kL);
-    for (int q = lo; q < hi; ++q) {
-      double* x = Qt + q * kL;
-      for (int r = 0; r < n; ++r)
-        std::copy(x + (size_t)r * ld, x + (size_t)r * ld + kL, &band[(size_t)r * kL]);
-      rotate_block(rots.data(), rots.size(), band.data());
-      for (int r = 0; r < n; ++r)
-        std::copy(&band[(size_t)r * kL], &band[(size_t)r * kL] + kL, x + (size_t)r * ld);
-    }
-  });
+  deal_blocks(0, blocks(n), 6.0 * (double)rots.size() * n, kSplitOnce,
+              [&](int q) { rotate_block(rots.data(), rots.size(), &Qt[(size_t)q * n * kL]); });
 }
 
 // One implicit Wilkinson-shifted QR step on the unreduced block [lo, hi] of
@@ -371,22 +402,20 @@ void qr_step(int lo, int hi, double* d, double* e, std::vector<Rot>& rots) {
 
 }  // namespace
 
+long host_pool_runs() { return Workers::get().runs(); }
+
 int host_syev(int n, double* Ain, double* w) {
   if (n <= 0) return 0;
-  const int ld = padded(n);
-  std::vector<double> A((size_t)(n + 1) * ld, 0.0), V((size_t)(n + 1) * ld, 0.0), beta(n, 0.0);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j)
-      A[(size_t)i * ld + j] = 0.5 * (Ain[(size_t)i * n + j] + Ain[(size_t)j * n + i]);
+  const int nq = blocks(n), ld = nq * kL;
+  std::vector<double> A((size_t)nq * n * kL, 0.0), V((size_t)n * ld, 0.0), beta(n, 0.0);
+  for (int q = 0; q < nq; ++q)
+    for (int i = 0; i < n; ++i)
+      for (int j = q * kL; j < std::min(n, (q + 1) * kL); ++j)
+        A[((size_t)q * n + i) * kL + j % kL] = 0.5 * (Ain[(size_t)i * n + j] + Ain[(size_t)j * n + i]);
   std::vector<double> d(n), e(n);
   householder_tridiag(n, ld, A, V, beta, d, e);
-  std::fill(V.begin() + (size_t)(n > 2 ? n - 2 : 0) * ld, V.end(), 0.0);
-  std::fill(A.begin(), A.end(), 0.0);
-  form_q(n, ld, V, beta, A);
-  std::vector<double>& Qv = V;  // the eigenvectors' rows, from Q^T
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) Qv[(size_t)i * ld + j] = A[(size_t)j * ld + i];
-  double* Qt = Qv.data();
+  std::vector<double>& Qt = A;
+  form_qt(n, ld, V, beta, Qt);
   std::vector<Rot> rots;
   const size_t flush_at = (size_t)1 << 20;
   rots.reserve(std::min(flush_at, (size_t)n * n));
@@ -403,19 +432,19 @@ int host_syev(int n, double* Ain, double* w) {
     if (lo > 0) e[lo - 1] = 0.0;
     qr_step(lo, hi, d.data(), e.data(), rots);
     if (rots.size() >= flush_at) {
-      apply_rotations(n, rots, Qt, ld);
+      apply_rotations(n, rots, Qt);
       rots.clear();
     }
     if (++guard > 60 * n + 100) return 1;
   }
-  apply_rotations(n, rots, Qt, ld);
+  apply_rotations(n, rots, Qt);
   std::vector<int> idx(n);
   for (int i = 0; i < n; ++i) idx[i] = i;
   std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return d[x] < d[y]; });
-  for (int j = 0; j < n; ++j) {
-    w[j] = d[idx[j]];
-    for (int i = 0; i < n; ++i) Ain[(size_t)i * n + j] = Qt[(size_t)idx[j] * ld + i];
-  }
+  for (int j = 0; j < n; ++j) w[j] = d[idx[j]];
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j)
+      Ain[(size_t)i * n + j] = Qt[((size_t)(i / kL) * n + idx[j]) * kL + i % kL];
   return 0;
 }
 
@@ -428,7 +457,7 @@ int host_cholesky(int n, double* A) {
   for (int j = 0; j < n; ++j) {
     double* x = &U[(size_t)j * ld + j];  // rows j.. of column j
     const int m = n - j;
-    split_range((m + kL - 1) / kL, 2.0 * m * (double)j, kSplitStep, [&](int lo, int hi) {
+    split_range((m + kL - 1) / kL, 2.0 * m * (double)j, kSplitColumn, [&](int lo, int hi) {
       std::vector<double> f(j);
       for (int k = 0; k < j; ++k) f[k] = U[(size_t)k * ld + j];
       for (int q = lo; q < hi; ++q) fold_block(j, f.data(), &U[j + q * kL], ld, x + q * kL);
