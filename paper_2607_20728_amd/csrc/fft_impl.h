@@ -755,11 +755,34 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_fwd_ip(const cplx*
   }
 }
 
+// the sphere entries e of plane pl of grid g from its rows of coefficients:
+// put(position in the plane, value)
+template <class PUT>
+__device__ __forceinline__ void sphere_entries(const PlaneArgs& pa, long g, int pl, int nt, PUT put) {
+  const long set = g / pa.nvh;
+  const int p = (int)(g % pa.nvh);
+  const double* x1 = pa.X + (set * pa.nv + 2 * p) * (long)pa.npw;
+  const double* x2 = (2 * p + 1 < pa.nv) ? x1 + pa.npw : nullptr;
+  for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += nt) {
+    const int code = pa.ent_code[e];
+    cplx h;
+    if (code == 0) {
+      h = mk(x1[0] * pa.s0, x2 ? x2[0] * pa.s0 : 0.0);
+    } else {
+      const int k = abs(code) - 1;
+      const double c1 = x1[1 + 2 * k], q1 = x1[2 + 2 * k];
+      const double c2 = x2 ? x2[1 + 2 * k] : 0.0, q2 = x2 ? x2[2 + 2 * k] : 0.0;
+      h = code > 0 ? mk((c1 + q2) * pa.s1, (c2 - q1) * pa.s1)
+                   : mk((c1 - q2) * pa.s1, (q1 + c2) * pa.s1);
+    }
+    put(pa.ent_pos[e], h);
+  }
+}
+
 // Inverse, in place: the modes scattered into a cleared plane, the rows that
 // hold some, then all columns, whose last pass writes the plane to memory.
 // 800 FP64 grids of 64^3: 0.84 ms with scratch lines beside a compact block,
-// now 0.69; 720 FP32 grids of 48^3: 0.27 and 0.21; 1,024 FP64 grids of 72^3,
-// one workgroup per CU instead of two: 1.01 and 1.13.
+// now 0.69; 720 FP32 grids of 48^3: 0.27 and 0.21.
 template <int N2, int N3>
 __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data, PlaneArgs pa,
                                                                     const cplx* __restrict__ tw2,
@@ -774,27 +797,7 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data,
   cplx* gp = data + g * pa.nr + (long)pa.plane_i1[pl] * NP2;
   for (int e = threadIdx.x; e < N2 * RS; e += NT) P[e] = mk(0.0, 0.0);
   __syncthreads();
-  {
-    const long set = g / pa.nvh;
-    const int p = (int)(g % pa.nvh);
-    const double* x1 = pa.X + (set * pa.nv + 2 * p) * (long)pa.npw;
-    const double* x2 = (2 * p + 1 < pa.nv) ? x1 + pa.npw : nullptr;
-    for (int e = pa.plane_off[pl] + threadIdx.x; e < pa.plane_off[pl + 1]; e += NT) {
-      const int code = pa.ent_code[e];
-      cplx h;
-      if (code == 0) {
-        h = mk(x1[0] * pa.s0, x2 ? x2[0] * pa.s0 : 0.0);
-      } else {
-        const int k = abs(code) - 1;
-        const double c1 = x1[1 + 2 * k], q1 = x1[2 + 2 * k];
-        const double c2 = x2 ? x2[1 + 2 * k] : 0.0, q2 = x2 ? x2[2 + 2 * k] : 0.0;
-        h = code > 0 ? mk((c1 + q2) * pa.s1, (c2 - q1) * pa.s1)
-                     : mk((c1 - q2) * pa.s1, (q1 + c2) * pa.s1);
-      }
-      const int pos = pa.ent_pos[e];
-      P[pos / N3 * RS + pos % N3] = h;
-    }
-  }
+  sphere_entries(pa, g, pl, NT, [=](int pos, cplx h) { P[pos / N3 * RS + pos % N3] = h; });
   __syncthreads();
   auto none = [](int, int) { return 0; };
   // row l of the kept set is n2 = l - m2
@@ -806,6 +809,58 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data,
   auto col = [=](int k, int l) { return P + k * RS + l; };
   lines_inplace<N2, 1, N3, NT, 0, 1>(
       NlAll<N3>(), col, none, [=](int k, int l, cplx v, int) { gp[k * N3 + l] = v; }, tw2);
+}
+
+// Inverse where the padded plane leaves room for one workgroup on a CU (72^2 in
+// FP64): only the 2 m2 + 1 rows that hold modes are kept, in a compact block,
+// and the columns read it (zeros elsewhere) in batches of LB lines through a
+// scratch buffer, the last pass writing LB adjacent columns to memory.  Two
+// workgroups share a CU while the block and the buffer take half its LDS.
+// 400 grids of 72^3 (43 planes and rows): 0.61 ms, in place 0.67; 14 planes' worth
+// of one vector's 50 grids: 88 us, in place 101.
+constexpr size_t kHalfLds = 81920;
+template <int N2, int N3>
+constexpr bool sphere_rows_ok() {
+  return plane_nscratch<N2, N3>() == 1 && wp_lds<N2, N3>() > kHalfLds;
+}
+template <int N2, int N3>
+constexpr size_t sphere_rows_lds(int m2, int lb) {
+  return sizeof(cplx) * ((size_t)(2 * m2 + 1) * N3 + (size_t)(N2 > N3 ? N2 : N3) * lb);
+}
+template <int N2, int N3, int LB>
+__global__ __launch_bounds__(kPlaneThreads) void k_sphere_inv_rows(cplx* data, PlaneArgs pa,
+                                                                    const cplx* __restrict__ tw2,
+                                                                    const cplx* __restrict__ tw3) {
+  constexpr int NT = kPlaneThreads;
+  static_assert(factor(N2).n == 2 && factor(N3).n == 2, "one scratch buffer serves two passes");
+  extern __shared__ cplx lds[];
+  const int m2 = pa.m2, K2 = 2 * pa.m2 + 1;
+  cplx* Q = lds;  // [K2][N3], row l is n2 = l - m2
+  cplx* S = Q + K2 * N3;
+  long g;
+  int pl;
+  xcd_item(blockIdx.x, pa.nplanes, pa.group != 0, g, pl);
+  if (g >= pa.batch) return;
+  cplx* gp = data + g * pa.nr + (long)pa.plane_i1[pl] * (N2 * N3);
+  auto image = [=](int n2) { return (n2 < (N2 + 1) / 2 ? n2 : n2 - N2) + m2; };
+  for (int e = threadIdx.x; e < K2 * N3; e += NT) Q[e] = mk(0.0, 0.0);
+  __syncthreads();
+  sphere_entries(pa, g, pl, NT,
+                 [=](int pos, cplx h) { Q[image(pos / N3) * N3 + pos % N3] = h; });
+  __syncthreads();
+#pragma unroll 1
+  for (int l0 = 0; l0 < K2; l0 += LB)
+    ct_passes<N3, 1, LB, NT, 0, 1, 1, N3, 1, N3>(Q + l0 * N3, S, S, Q + l0 * N3, min(LB, K2 - l0),
+                                                 tw3);
+#pragma unroll 1
+  for (int l0 = 0; l0 < N3; l0 += LB) {
+    auto ld = [=](int k, int l) -> cplx {
+      const int q = image(k);
+      return q >= 0 && q < K2 ? Q[q * N3 + l0 + l] : mk(0.0, 0.0);
+    };
+    auto st = [=](int k, int l, cplx v) { gp[k * N3 + l0 + l] = v; };
+    fn_passes<N2, 1, LB, NT, 0, 1>(ld, st, S, S, min(LB, N3 - l0), tw2);
+  }
 }
 
 template <int N>
@@ -1382,6 +1437,26 @@ int set_ct_lds_limits(int n2, int n3, int n1) {
   return BSE_OK;
 }
 
+// the compact inverse, in the larger batch that leaves two workgroups on a CU;
+// false where neither does
+template <int N2, int N3>
+bool launch_sphere_rows(dim3 grid, hipStream_t st, cplx* data, PlaneArgs pa, const cplx* tw2,
+                        const cplx* tw3) {
+  if constexpr (sphere_rows_ok<N2, N3>()) {
+    const size_t big = sphere_rows_lds<N2, N3>(pa.m2, 36), small = sphere_rows_lds<N2, N3>(pa.m2, 18);
+    if (big <= kHalfLds)
+      hipLaunchKernelGGL((k_sphere_inv_rows<N2, N3, 36>), grid, dim3(kPlaneThreads), big, st, data,
+                         pa, tw2, tw3);
+    else if (small <= kHalfLds)
+      hipLaunchKernelGGL((k_sphere_inv_rows<N2, N3, 18>), grid, dim3(kPlaneThreads), small, st, data,
+                         pa, tw2, tw3);
+    else
+      return false;
+    return true;
+  }
+  return false;
+}
+
 // pruned sphere-plane launches: false when the size has no compiled kernel
 // or the plane does not fit the device's LDS
 bool launch_sphere_ct(int n2, int n3, bool inverse, size_t max_lds, dim3 grid, hipStream_t st,
@@ -1390,6 +1465,7 @@ bool launch_sphere_ct(int n2, int n3, bool inverse, size_t max_lds, dim3 grid, h
   if (n2 == A && n3 == B) {                                                                   \
     constexpr size_t shm = wp_lds<A, B>();                                                    \
     if (shm > max_lds) return false;                                                          \
+    if (inverse && launch_sphere_rows<A, B>(grid, st, data, pa, ay.tw, az.tw)) return true;   \
     if (inverse)                                                                              \
       hipLaunchKernelGGL((k_sphere_inv_ip<A, B>), grid, dim3(wp_nt<A, B>()), shm, st, data, pa, \
                          ay.tw, az.tw);                                                       \
@@ -1403,6 +1479,16 @@ bool launch_sphere_ct(int n2, int n3, bool inverse, size_t max_lds, dim3 grid, h
   return false;
 }
 
+template <int N2, int N3>
+int set_sphere_rows_lds() {
+  if constexpr (sphere_rows_ok<N2, N3>()) {
+    for (const void* f : {(const void*)k_sphere_inv_rows<N2, N3, 36>,
+                          (const void*)k_sphere_inv_rows<N2, N3, 18>})
+      BSE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHalfLds));
+  }
+  return BSE_OK;
+}
+
 // the pruned kernels may use up to the device's LDS
 int set_sphere_lds_limits(int n2, int n3, size_t max_lds) {
 #define C(A, B)                                                                               \
@@ -1412,6 +1498,7 @@ int set_sphere_lds_limits(int n2, int n3, size_t max_lds) {
                          (const void*)k_sphere_inv_ip<A, B>};                                 \
     for (const void* f : fns)                                                                 \
       BSE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim));       \
+    BSE_TRY((set_sphere_rows_lds<A, B>()));                                                   \
   }
   BSEX_PLANE_SIZES(C)
 #undef C
