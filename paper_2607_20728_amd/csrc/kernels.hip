@@ -163,14 +163,14 @@ __global__ void k_real_part(const double2* __restrict__ g, long nr, double* __re
 // groups)), so each phi_v(r) is read once per group rather than once per pair
 // of vectors.  Bound by HBM on a large grid.  A small one leaves too few waves
 // in flight at 8 vectors a thread, and takes 2 (1 for a single vector), phi
-// then coming from L2; four orbital pairs are loaded at a time.  Vectors past
-// the last are read as it, so the loads need no branch.
+// then coming from L2; two or four orbital pairs are loaded at a time.
+// Vectors past the last are read as it, so the loads need no branch.
 template <typename V2, typename R, int TB>
 __global__ __launch_bounds__(256) void k_transition_density(const V2* __restrict__ phir,
                                                             const V2* __restrict__ a, int nvh,
                                                             int nb, long nr,
                                                             V2* __restrict__ drho) {
-  constexpr int PB = TB == 8 ? 2 : 4;
+  constexpr int PB = TB > 4 ? 2 : 4;
   const long r = (long)blockIdx.x * 256 + threadIdx.x;
   if (r >= nr) return;
   const int b0 = blockIdx.y * TB;
@@ -202,6 +202,35 @@ __global__ __launch_bounds__(256) void k_transition_density(const V2* __restrict
       drho[(long)((b0 + o) / 2) * nr + r] = out;
     }
   }
+}
+
+// Up to 7 vectors, the loads of one at a time behind a test: where a packed grid
+// is about 3 MB or more, several vectors' reads in flight at once are slower.
+template <typename V2, typename R>
+__global__ __launch_bounds__(256) void k_transition_density_few(const V2* __restrict__ phir,
+                                                                const V2* __restrict__ a, int nvh,
+                                                                int nb, long nr,
+                                                                V2* __restrict__ drho) {
+  const long r = (long)blockIdx.x * 256 + threadIdx.x;
+  if (r >= nr) return;
+  R s[8] = {};
+  for (int p = 0; p < nvh; ++p) {
+    const V2 f = phir[(long)p * nr + r];
+#pragma unroll
+    for (int o = 0; o < 7; ++o)
+      if (o < nb) {
+        const V2 v = a[((long)o * nvh + p) * nr + r];
+        s[o] += f.x * v.x + f.y * v.y;
+      }
+  }
+#pragma unroll
+  for (int o = 0; o < 7; o += 2)
+    if (o < nb) {
+      V2 out;
+      out.x = s[o];
+      out.y = s[o + 1];
+      drho[(long)(o / 2) * nr + r] = out;
+    }
 }
 
 template <typename V2, typename R>
@@ -1195,28 +1224,60 @@ int real_part(const double2* grid, long nr, double* out, hipStream_t st) {
   return BSE_OK;
 }
 
-// 8 vectors a thread from 2^18 points on (8 vectors of 200 bands at 64^3, FP64:
-// 0.67 ms, 1.01 with 2), below that 2: 5 vectors of 107 bands at 32^3 take
-// 26 us, with 8 a thread and one orbital pair at a time 96; 8 of 180 at 48^3 in
-// FP32 0.20 and 0.39 ms; 5 of 16 at 24^3 3.5 and 14 us
+// 2 vectors a thread on a small grid: below 2^17 points in FP64 and 40,000 in
+// FP32.  From there on 8, and a remainder in a group of its own size; where a
+// packed grid takes 2.75 MB or more, read one vector at a time.
+// 8 vectors of 120 bands, 2 and 8 a thread, us: FP64 40^3 167 / 267, 50^3 276 / 290,
+// 54^3 343 / 308, 60^3 517 / 398; FP32 32^3 (48 bands) 9.5 / 13.6, 36^3 38 / 37, 40^3
+// 54 / 44, 48^3 140 / 122, 60^3 261 / 242.
+// 3 of 120 bands in a group of 3 and one at a time: FP64 54^3 (2.5 MB) 133 / 140,
+// 60^3 (3.5 MB) 226 / 208, 64^3 271 / 247; FP32 64^3 (2.1 MB) 126 / 136, 72^3 (3.0 MB)
+// 198 / 190.
+template <int TB, typename V2, typename R>
+static void launch_density_group(const V2* phir, const V2* a, int nvh, int nb, long nr, V2* drho,
+                                 hipStream_t st) {
+  const dim3 grid((unsigned)((nr + 255) / 256), (unsigned)((nb + TB - 1) / TB));
+  hipLaunchKernelGGL((k_transition_density<V2, R, TB>), grid, dim3(256), 0, st, phir, a, nvh, nb, nr,
+                     drho);
+}
+
 template <typename V2, typename R>
 static int launch_transition_density(const V2* phir, const V2* a, int nv, int nb, long nr, V2* drho,
                                      hipStream_t st) {
   if (nb <= 0 || nr <= 0) return BSE_OK;
-  const int tb = nb == 1 ? 1 : nb == 2 || nr < (1L << 18) ? 2 : 8;
-  const long gx = (nr + 255) / 256, gy = ((long)nb + tb - 1) / tb;
-  if (gx > 0x7fffffffL || gy > 65535) return fail(BSE_EINVAL, "transition density: block too large");
-  const dim3 grid((unsigned)gx, (unsigned)gy);
   const int nvh = (nv + 1) / 2;
-  if (tb == 1)
-    hipLaunchKernelGGL((k_transition_density<V2, R, 1>), grid, dim3(256), 0, st, phir, a, nvh, nb,
-                       nr, drho);
-  else if (tb == 2)
-    hipLaunchKernelGGL((k_transition_density<V2, R, 2>), grid, dim3(256), 0, st, phir, a, nvh, nb,
-                       nr, drho);
-  else
-    hipLaunchKernelGGL((k_transition_density<V2, R, 8>), grid, dim3(256), 0, st, phir, a, nvh, nb,
-                       nr, drho);
+  const bool small = nr < (sizeof(R) == 8 ? 1L << 17 : 40000L);
+  const bool large = nr * (long)sizeof(V2) >= 2750000L;
+  const int tb = small ? std::min(nb, 2) : 8;
+  if ((nr + 255) / 256 > 0x7fffffffL || ((long)nb + tb - 1) / tb > 65535)
+    return fail(BSE_EINVAL, "transition density: block too large");
+  const int full = tb == 8 ? nb / 8 * 8 : nb, rest = nb - full;
+  if (full > 0) {
+    if (tb == 1)
+      launch_density_group<1, V2, R>(phir, a, nvh, full, nr, drho, st);
+    else if (tb == 2)
+      launch_density_group<2, V2, R>(phir, a, nvh, full, nr, drho, st);
+    else
+      launch_density_group<8, V2, R>(phir, a, nvh, full, nr, drho, st);
+  }
+  const V2* ar = a + (long)full * nvh * nr;
+  V2* dr = drho + (long)(full / 2) * nr;
+  if (rest > 0 && large) {
+    hipLaunchKernelGGL((k_transition_density_few<V2, R>), dim3((unsigned)((nr + 255) / 256)),
+                       dim3(256), 0, st, phir, ar, nvh, rest, nr, dr);
+    CHECK_LAUNCH();
+    return BSE_OK;
+  }
+#define GO(TB) \
+  if (rest == TB) launch_density_group<TB, V2, R>(phir, ar, nvh, rest, nr, dr, st)
+  GO(1);
+  GO(2);
+  GO(3);
+  GO(4);
+  GO(5);
+  GO(6);
+  GO(7);
+#undef GO
   CHECK_LAUNCH();
   return BSE_OK;
 }
