@@ -535,10 +535,11 @@ template <int N2, int N3>
 constexpr size_t wp_lds() {
   return sizeof(cplx) * (size_t)N2 * wp_rs<N2, N3>();
 }
-// threads: one butterfly each in the passes of radix 4 and more
+// threads: one butterfly each in the passes of radix 4 and more, and at least
+// `least`
 template <int N2, int N3>
-constexpr int wp_nt() {
-  int t = 64;
+constexpr int plane_nt(int least) {
+  int t = least;
   const Fac a = factor(N2), b = factor(N3);
   for (int p = 0; p < a.n; ++p)
     if (a.r[p] >= 4 && N2 / a.r[p] * N3 > t) t = N2 / a.r[p] * N3;
@@ -546,6 +547,19 @@ constexpr int wp_nt() {
     if (b.r[p] >= 4 && N3 / b.r[p] * N2 > t) t = N3 / b.r[p] * N2;
   t = (t + 63) / 64 * 64;
   return t > 768 ? 768 : t;
+}
+// A plane of at most 16 x 16 has so few butterflies that one wave's loads and
+// stores are what takes the time, and the sphere passes, whose launches are
+// small, gain from more waves up to 24 x 24.  With 64 / 128 / 256 threads, FP64:
+// 16^2 forward, 54 planes 5.4 / 4.7 / 4.2 us, W planes, 1,536 9.7 / 8.6 / 8.4; with
+// 128 / 256, 24^2 inverse, 240 planes 7.1 / 6.3, but W planes, 7,680 39.3 / 40.9.
+template <int N2, int N3>
+constexpr int wp_nt() {
+  return plane_nt<N2, N3>(N2 * N3 <= 256 ? 256 : 64);
+}
+template <int N2, int N3>
+constexpr int sp_nt() {
+  return plane_nt<N2, N3>(256);
 }
 
 // line and butterfly of task u of nl lines (nl a constant, or NlDiv with the
@@ -724,10 +738,10 @@ __global__ __launch_bounds__((wp_nt<N2, N3>())) void k_w_plane(cplx* data, int N
 // FP32 grids of 48 x 48 x 120 took 11.9 ms, now 5.8; 10,400 FP64 grids of 64^3
 // 11.4, now 6.9 (3.9 TB/s).
 template <int N2, int N3>
-__global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_fwd_ip(const cplx* data, PlaneArgs pa,
+__global__ __launch_bounds__((sp_nt<N2, N3>())) void k_sphere_fwd_ip(const cplx* data, PlaneArgs pa,
                                                                     const cplx* __restrict__ tw2,
                                                                     const cplx* __restrict__ tw3) {
-  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = wp_nt<N2, N3>();
+  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = sp_nt<N2, N3>();
   static_assert(factor(N2).n >= 2 && factor(N3).n >= 2, "plane lengths need two passes");
   extern __shared__ cplx lds[];
   cplx* P = lds;
@@ -784,10 +798,10 @@ __device__ __forceinline__ void sphere_entries(const PlaneArgs& pa, long g, int 
 // 800 FP64 grids of 64^3: 0.84 ms with scratch lines beside a compact block,
 // now 0.69; 720 FP32 grids of 48^3: 0.27 and 0.21.
 template <int N2, int N3>
-__global__ __launch_bounds__((wp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data, PlaneArgs pa,
+__global__ __launch_bounds__((sp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data, PlaneArgs pa,
                                                                     const cplx* __restrict__ tw2,
                                                                     const cplx* __restrict__ tw3) {
-  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = wp_nt<N2, N3>();
+  constexpr int NP2 = N2 * N3, RS = wp_rs<N2, N3>(), NT = sp_nt<N2, N3>();
   extern __shared__ cplx lds[];
   cplx* P = lds;
   long g;
@@ -1467,10 +1481,10 @@ bool launch_sphere_ct(int n2, int n3, bool inverse, size_t max_lds, dim3 grid, h
     if (shm > max_lds) return false;                                                          \
     if (inverse && launch_sphere_rows<A, B>(grid, st, data, pa, ay.tw, az.tw)) return true;   \
     if (inverse)                                                                              \
-      hipLaunchKernelGGL((k_sphere_inv_ip<A, B>), grid, dim3(wp_nt<A, B>()), shm, st, data, pa, \
+      hipLaunchKernelGGL((k_sphere_inv_ip<A, B>), grid, dim3(sp_nt<A, B>()), shm, st, data, pa, \
                          ay.tw, az.tw);                                                       \
     else                                                                                      \
-      hipLaunchKernelGGL((k_sphere_fwd_ip<A, B>), grid, dim3(wp_nt<A, B>()), shm, st, data, pa, \
+      hipLaunchKernelGGL((k_sphere_fwd_ip<A, B>), grid, dim3(sp_nt<A, B>()), shm, st, data, pa, \
                          ay.tw, az.tw);                                                       \
     return true;                                                                              \
   }
