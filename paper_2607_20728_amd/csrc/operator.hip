@@ -5,6 +5,7 @@
 #include <cmath>
 
 #include "context.h"
+#include "scratch_fit.h"
 
 namespace bsex {
 
@@ -229,18 +230,19 @@ static int ensure_ov(bse_ctx* c, int nset) {
   return ctx_alloc_t(c, &c->Ov, need);
 }
 
-// the context-owned split-K workspace, at least `need` doubles; it grows by
-// more than was asked, so a solver's growing products do not replace it (and
-// drop the graphs that reference it) at every step
+// the context-owned split-K workspace, at least `need` doubles (replacing it
+// drops the graphs that reference it)
 int ensure_gw(bse_ctx* c, long need) {
-  if (need <= c->gw_len) return BSE_OK;
-  const long len = std::max(need, std::min(2 * c->gw_len, c->gw_len + (4L << 20)));
+  const long have = c->gw_len;
+  if (need <= have) return BSE_OK;
   ctx_release(c, c->gw);
   c->gw = nullptr;
   c->gw_len = 0;
-  BSE_TRY(ctx_alloc_t(c, &c->gw, (size_t)len));
-  c->gw_len = len;
-  return BSE_OK;
+  return grow_scratch(have, need, [&](long len) {
+    const int rc = ctx_alloc_t(c, &c->gw, (size_t)len);
+    if (rc == BSE_OK) c->gw_len = len;
+    return rc;
+  });
 }
 
 // GEMM with a context-owned split-K workspace
