@@ -52,6 +52,7 @@ struct bse_ctx {
   // PDEP work of the exchange form of W (coupling beyond the TDA):
   // sphere coefficients [nv][npw], PDEP projections [nv][npdep], result [nv][npw]
   int wx_sets = 0;            // bands that the next four hold
+  int wx_limit = 0;           // most bands that fit (0: not known to be limited)
   double *wx_RS = nullptr, *wx_T = nullptr, *wx_F = nullptr;
   double2* wx_cmp = nullptr;  // [wx_sets][nvh][npw] sphere entries of the pair transforms
   double2* xgrid = nullptr;   // [xgrid_sets][nvh][nr] -alpha K_x a of an apply block

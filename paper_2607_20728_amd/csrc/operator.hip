@@ -677,10 +677,7 @@ static int wx_sets(const bse_ctx* c, int nx) {
 
 // scratch of `sets` bands: pair grids and, for the PDEP part, their sphere
 // rows (two per grid), coefficients and compact entries
-static int ensure_wx(bse_ctx* c, int sets, bool pdep) {
-  BSE_TRY(ensure_xpair(c, sets));
-  if (!pdep || c->wx_sets >= sets) return BSE_OK;
-  const size_t rows = 2 * (size_t)sets * c->nvh, npw = c->basis.npw;
+static void drop_wx(bse_ctx* c) {
   ctx_release(c, c->wx_RS);
   ctx_release(c, c->wx_T);
   ctx_release(c, c->wx_F);
@@ -688,6 +685,12 @@ static int ensure_wx(bse_ctx* c, int sets, bool pdep) {
   c->wx_RS = c->wx_T = c->wx_F = nullptr;
   c->wx_cmp = nullptr;
   c->wx_sets = 0;
+}
+static int ensure_wx(bse_ctx* c, int sets, bool pdep) {
+  BSE_TRY(ensure_xpair(c, sets));
+  if (!pdep || c->wx_sets >= sets) return BSE_OK;
+  const size_t rows = 2 * (size_t)sets * c->nvh, npw = c->basis.npw;
+  drop_wx(c);
   BSE_TRY(ctx_alloc_t(c, &c->wx_RS, rows * npw));
   BSE_TRY(ctx_alloc_t(c, &c->wx_T, rows * c->npdep));
   BSE_TRY(ctx_alloc_t(c, &c->wx_F, rows * npw));
@@ -709,11 +712,16 @@ static int w_exchange_like(bse_ctx* c, const double2* L, const double2* M, const
   SphereMap m = c->map;
   const bool planes = w_planes_on(c, false);
   const bool fused = planes || w_fused_on(), pairs = w_pairs_on(c, false);
-  int nk = planes && pairs ? wx_sets(c, nx) : 1;
-  if (ensure_wx(c, nk, pdep) != BSE_OK) {
-    nk = 1;  // as little scratch as there can be
-    BSE_TRY(ensure_wx(c, nk, pdep));
-  }
+  int nk = 1;
+  BSE_TRY(fit_sets(planes && pairs ? wx_sets(c, nx) : 1, &c->wx_limit,
+                   [&](int sets) { return ensure_wx(c, sets, pdep); },
+                   [&] {
+                     drop_wx(c);
+                     ctx_release(c, c->xpair);
+                     c->xpair = nullptr;
+                     c->xpair_sets = 0;
+                   },
+                   &nk));
   double2* P = c->xpair;
   for (int v = 0; v < nx; v += nk) {
     const double2* xv = x + (long)(v >> 1) * nr;

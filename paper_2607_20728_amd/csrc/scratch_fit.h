@@ -18,4 +18,17 @@ int grow_scratch(long have, long need, Alloc&& alloc) {
   return rc == BSE_ENOMEM && roomy > need ? alloc(need) : rc;
 }
 
+// Scratch for `want` sets at a time, or for one where that is out of memory:
+// drop() then gives back everything that a failed alloc(want) left, and *limit
+// (0: none yet) keeps later calls from trying again.  *sets: what there is.
+template <class Alloc, class Drop>
+int fit_sets(int want, int* limit, Alloc&& alloc, Drop&& drop, int* sets) {
+  *sets = *limit > 0 ? std::min(want, *limit) : want;
+  const int rc = alloc(*sets);
+  if (rc != BSE_ENOMEM || *sets == 1) return rc;
+  drop();
+  *limit = *sets = 1;
+  return alloc(1);
+}
+
 }  // namespace bsex

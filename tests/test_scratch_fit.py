@@ -46,6 +46,60 @@ int main() {
 }
 """
 
+# one call's buffers as the coupling's bands need them: pair grids of 10 units a
+# set that stay when the second buffer, 4 a set, is out of memory
+SETS = r"""
+struct Mem {
+  int free, grids = 0, rows = 0, tries = 0;
+  int alloc(int sets) {
+    ++tries;
+    if (grids < sets) {
+      free += 10 * grids;
+      grids = 0;
+      if (10 * sets > free) return BSE_ENOMEM;
+      free -= 10 * (grids = sets);
+    }
+    if (rows < sets) {
+      free += 4 * rows;
+      rows = 0;
+      if (4 * sets > free) return BSE_ENOMEM;
+      free -= 4 * (rows = sets);
+    }
+    return BSE_OK;
+  }
+  void drop() {
+    free += 10 * grids + 4 * rows;
+    grids = rows = 0;
+  }
+};
+
+int main() {
+  struct { int free, want, sets, rc, limit; } t[] = {
+      {200, 8, 8, BSE_OK, 0},      {112, 8, 8, BSE_OK, 0},      {111, 8, 1, BSE_OK, 1},
+      {80, 8, 1, BSE_OK, 1},       {14, 8, 1, BSE_OK, 1},       {13, 8, 1, BSE_ENOMEM, 1},
+      {14, 1, 1, BSE_OK, 0},       {13, 1, 1, BSE_ENOMEM, 0}};
+  for (auto& c : t) {
+    Mem m{c.free};
+    int limit = 0, sets = 0;
+    auto call = [&](int want) {
+      return fit_sets(want, &limit, [&](int n) { return m.alloc(n); }, [&] { m.drop(); }, &sets);
+    };
+    CHECK(call(c.want) == c.rc && sets == c.sets && limit == c.limit);
+    if (c.rc != BSE_OK) continue;
+    // what one set does not need is free, and a later call does not try again
+    CHECK(m.free == c.free - 14 * c.sets);
+    const int tries = m.tries;
+    CHECK(call(c.want) == BSE_OK && sets == c.sets && m.tries == tries + 1);
+    CHECK(m.free == c.free - 14 * c.sets);
+  }
+  int limit = 0, sets = 0, n = 0, drops = 0;  // another error is passed on at once
+  CHECK(fit_sets(8, &limit, [&](int) { ++n; return (int)BSE_EHIP; }, [&] { ++drops; }, &sets) ==
+        BSE_EHIP);
+  CHECK(n == 1 && drops == 0 && limit == 0);
+  return 0;
+}
+"""
+
 
 def _run(tmp_path, body):
     gxx = shutil.which("g++")
@@ -62,3 +116,7 @@ def _run(tmp_path, body):
 
 def test_workspace_growth(tmp_path):
     _run(tmp_path, GROW)
+
+
+def test_sets_fall_back_to_one(tmp_path):
+    _run(tmp_path, SETS)
