@@ -9,7 +9,8 @@ namespace bsex {
 
 enum Phase {
   PH_PROJ = 0,   // occupied projector (overlap and update GEMMs)
-  PH_FFT_INV,    // sphere -> grid scatter and inverse transforms
+  PH_FFT_INV,    // sphere -> grid scatter and inverse transforms (with V x and the forward
+                 // axis pass in H x, where they are one kernel with the inverse one)
   PH_K1E,        // transition density and Poisson solve
   PH_TAU_STREAM, // tau contraction over the cached blocks (K1d)
   PH_TAU_TILE,   // tau contraction over blocks rebuilt during the call
