@@ -830,8 +830,8 @@ __global__ __launch_bounds__((sp_nt<N2, N3>())) void k_sphere_inv_ip(cplx* data,
 // and the columns read it (zeros elsewhere) in batches of LB lines through a
 // scratch buffer, the last pass writing LB adjacent columns to memory.  Two
 // workgroups share a CU while the block and the buffer take half its LDS.
-// 400 grids of 72^3 (43 planes and rows): 0.61 ms, in place 0.67; 14 planes' worth
-// of one vector's 50 grids: 88 us, in place 101.
+// FP64 grids of 72^3 with 43 planes and rows: 400 in 0.61 ms, in place 0.67; 50 in
+// 93 us, in place 101.
 constexpr size_t kHalfLds = 81920;
 template <int N2, int N3>
 constexpr bool sphere_rows_ok() {
